@@ -328,8 +328,11 @@ static size_t align256f(size_t x) { return (x + 255) / 256 * 256; }
 
 size_t fwd_workspace_bytes(int batch, int Hq, int Hkv, int N) {
     const int64_t rq = static_cast<int64_t>(batch) * Hq * N, rkv = static_cast<int64_t>(batch) * Hkv * N;
-    return align256f(4 * static_cast<size_t>(rq)) + block_flags_bytes(rq, rkv, static_cast<int64_t>(batch) * Hkv);
+    return align256f(4 * static_cast<size_t>(rq)) + PACE_BYTES +
+           block_flags_bytes(rq, rkv, static_cast<int64_t>(batch) * Hkv);
 }
+
+constexpr int64_t FWD_WAVE_MIN_ROWS = 1;
 
 template <typename T, int D>
 static hipError_t launch_fwd_t(const void* q, const void* k, const void* v, const int32_t* row_ptr,
@@ -340,15 +343,22 @@ static hipError_t launch_fwd_t(const void* q, const void* k, const void* v, cons
     if (rows == 0) return hipSuccess;
     const int64_t rows_kv = static_cast<int64_t>(batch) * Hkv * N;
     int32_t* order = static_cast<int32_t*>(ws);
-    const block_flag_layout fl = block_flags_at(static_cast<char*>(ws) + align256f(4 * static_cast<size_t>(rows)),
+    const block_flag_layout fl = block_flags_at(static_cast<char*>(ws) + align256f(4 * static_cast<size_t>(rows)) + PACE_BYTES,
                                                 rows, rows_kv, static_cast<int64_t>(batch) * Hkv);
-    hipError_t e = launch_lpt_order(row_ptr, rows, N, col_cap, order, s);
+    uint32_t* pace = reinterpret_cast<uint32_t*>(static_cast<char*>(ws) + align256f(4 * static_cast<size_t>(rows)));
+    hipError_t e = launch_lpt_order(row_ptr, rows, N, col_cap, order, pace, s);
     if (e != hipSuccess) return e;
     if (o_lo) {
         if constexpr (sizeof(T) == 2) {
             e = launch_block_flags(q, k, v, fl, rows, rows_kv, N, D, Hq, Hkv, cg, s);
             if (e != hipSuccess) return e;
         }
+    }
+    if constexpr (sizeof(T) == 2) {
+        if (rows >= FWD_WAVE_MIN_ROWS)
+            return launch_attn_fwd_wave(D, q, k, v, row_ptr, col_idx, col_cap, o, lse, o_lo, order, pace, rows, Hq, Hkv, N, cg, fl, s);
+    }
+    if (o_lo) {
         if (cg.padded) launch_fwd_k<T, D, true, true>(q, k, v, row_ptr, col_idx, col_cap, o, lse, o_lo, order, rows, Hq, Hkv, N, cg, fl, s);
         else launch_fwd_k<T, D, true, false>(q, k, v, row_ptr, col_idx, col_cap, o, lse, o_lo, order, rows, Hq, Hkv, N, cg, fl, s);
     } else {

@@ -106,7 +106,10 @@ __device__ void lpt_segment(const int32_t* __restrict__ ptr, int64_t cap, int32_
 // sorts each piece of the head that falls into one XCD range.
 __global__ __launch_bounds__(PLAN_NT) void lpt_order_kernel(const int32_t* __restrict__ ptr, int64_t nrows,
                                                             int64_t n_per_head, int64_t cap,
-                                                            int32_t* __restrict__ order) {
+                                                            int32_t* __restrict__ order,
+                                                            uint32_t* __restrict__ pace) {
+    if (pace && blockIdx.x == 0)
+        for (int i = threadIdx.x; i < static_cast<int>(PACE_BYTES / 4); i += PLAN_NT) pace[i] = 0u;
     __shared__ uint32_t hist[PLAN_CLASSES][PLAN_NT];
     __shared__ uint32_t part[PLAN_NT];
     __shared__ int64_t red[PLAN_NT / 64];
@@ -128,11 +131,11 @@ __global__ __launch_bounds__(PLAN_NT) void lpt_order_kernel(const int32_t* __res
 }
 
 hipError_t launch_lpt_order(const int32_t* ptr, int64_t nrows, int64_t n_per_head, int64_t cap, int32_t* order,
-                            hipStream_t s) {
+                            uint32_t* pace, hipStream_t s) {
     if (nrows <= 0) return hipSuccess;
     const int64_t heads = (nrows + n_per_head - 1) / n_per_head;
     hipLaunchKernelGGL(lpt_order_kernel, dim3(static_cast<unsigned>(heads)), dim3(PLAN_NT), 0, s, ptr, nrows,
-                       n_per_head, cap, order);
+                       n_per_head, cap, order, pace);
     return hipGetLastError();
 }
 
