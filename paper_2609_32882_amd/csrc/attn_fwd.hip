@@ -42,7 +42,7 @@ __global__ __launch_bounds__(AF_NT, 2) void attn_fwd_kernel(
     const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
     const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx, int64_t col_cap,
     T* __restrict__ o, float* __restrict__ lse, T* __restrict__ o_lo, int Hq, int Hkv, int N, float c_log2,
-    int period, const int32_t* __restrict__ order, cube_grid grid, block_flag_layout fl) {
+    int period, const int32_t* __restrict__ order, const float* __restrict__ even, cube_grid grid, block_flag_layout fl) {
     using F = typename frag_of<T>::type;
     constexpr bool SPLIT = COMP && sizeof(T) == 2;   // two-term P possible (bf16 only)
     constexpr int E = sizeof(T);
@@ -57,6 +57,7 @@ __global__ __launch_bounds__(AF_NT, 2) void attn_fwd_kernel(
     const int tid = threadIdx.x, lane = tid & 63, wave = wave_id(), half = lane >> 5;
     const int64_t row = work_row(order, xcd_item(blockIdx.x, gridDim.x), gridDim.x);
     const int64_t bh = row / N;
+    if (even && even[bh] > 0.f) return;      // a head of the one-wave kernel
     const int n = static_cast<int>(row % N);
     const int b = static_cast<int>(bh / Hq), h = static_cast<int>(bh % Hq);
     const int hkv = h / (Hq / Hkv);
@@ -313,26 +314,38 @@ __global__ __launch_bounds__(AF_NT, 2) void attn_fwd_kernel(
 
 template <typename T, int D, bool COMP, bool PAD>
 static void launch_fwd_k(const void* q, const void* k, const void* v, const int32_t* row_ptr, const int32_t* col_idx,
-                         int64_t col_cap, void* o, float* lse, void* o_lo, const int32_t* order, int64_t rows, int Hq,
-                         int Hkv, int N, const cube_grid& cg, const block_flag_layout& fl, hipStream_t s) {
+                         int64_t col_cap, void* o, float* lse, void* o_lo, const int32_t* order, const float* even,
+                         int64_t rows, int Hq, int Hkv, int N, const cube_grid& cg, const block_flag_layout& fl, hipStream_t s) {
     const float c = 1.4426950408889634f / sqrtf(static_cast<float>(D));
     hipLaunchKernelGGL((attn_fwd_kernel<T, D, COMP, PAD>), dim3(static_cast<unsigned>(rows)), dim3(AF_NT), 0, s,
                        static_cast<const T*>(q), static_cast<const T*>(k), static_cast<const T*>(v), row_ptr,
                        col_idx, col_cap, static_cast<T*>(o), lse, static_cast<T*>(o_lo), Hq, Hkv, N, c,
-                       resident_per_xcd<attn_fwd_kernel<T, D, COMP, PAD>>(AF_NT), order, cg, fl);
+                       resident_per_xcd<attn_fwd_kernel<T, D, COMP, PAD>>(AF_NT), order, even, cg, fl);
 }
 
-// Forward workspace: the work order of the CSR rows (one int32 per row), then
-// the block magnitude flags (used when the call keeps O's remainder).
+// Forward workspace: the work order of the CSR rows (one int32 per row), the
+// one-wave kernel's pacing words and the heads it takes (one float per query
+// head), then the block magnitude flags (used when the call keeps O's remainder).
 static size_t align256f(size_t x) { return (x + 255) / 256 * 256; }
 
 size_t fwd_workspace_bytes(int batch, int Hq, int Hkv, int N) {
     const int64_t rq = static_cast<int64_t>(batch) * Hq * N, rkv = static_cast<int64_t>(batch) * Hkv * N;
-    return align256f(4 * static_cast<size_t>(rq)) + PACE_BYTES +
+    return align256f(4 * static_cast<size_t>(rq)) + PACE_BYTES + align256f(4 * static_cast<size_t>(batch) * Hq) +
            block_flags_bytes(rq, rkv, static_cast<int64_t>(batch) * Hkv);
 }
 
-constexpr int64_t FWD_WAVE_MIN_ROWS = 1;
+// Rows from which bf16 problems with D = 128 also launch the one-wave kernel,
+// which takes the heads with even lists (about one length, 16 entries and up):
+// it keeps a SIMD per row, so it needs the chip's 1,024 SIMDs twice over, and
+// its fixed cost per row is not hidden by another wave.  Measured, us, this
+// kernel -> that one, top-k lists of k entries:
+//   rows      1,024 k 24   2,048 k 24   2,240 k 70   8,960 k 70   48,000 k 120
+//             78 -> 77     157 -> 147   504 -> 457   1627 -> 1434  15300 -> 13460
+//   below:    512 k 24 66 -> 69, 1,024 k 8 39 -> 43
+// Uneven lists (mass selection) ran 2-25% slower there, since nothing keeps
+// their walks together, and D = 64 5-25% (half the work per gathered byte and
+// per row), so both stay here.
+constexpr int64_t FWD_WAVE_MIN_ROWS = 2048;
 
 template <typename T, int D>
 static hipError_t launch_fwd_t(const void* q, const void* k, const void* v, const int32_t* row_ptr,
@@ -343,10 +356,13 @@ static hipError_t launch_fwd_t(const void* q, const void* k, const void* v, cons
     if (rows == 0) return hipSuccess;
     const int64_t rows_kv = static_cast<int64_t>(batch) * Hkv * N;
     int32_t* order = static_cast<int32_t*>(ws);
-    const block_flag_layout fl = block_flags_at(static_cast<char*>(ws) + align256f(4 * static_cast<size_t>(rows)) + PACE_BYTES,
-                                                rows, rows_kv, static_cast<int64_t>(batch) * Hkv);
-    uint32_t* pace = reinterpret_cast<uint32_t*>(static_cast<char*>(ws) + align256f(4 * static_cast<size_t>(rows)));
-    hipError_t e = launch_lpt_order(row_ptr, rows, N, col_cap, order, pace, s);
+    char* at = static_cast<char*>(ws) + align256f(4 * static_cast<size_t>(rows));
+    uint32_t* pace = reinterpret_cast<uint32_t*>(at);
+    float* even = reinterpret_cast<float*>(at + PACE_BYTES);
+    const block_flag_layout fl = block_flags_at(at + PACE_BYTES + align256f(4 * static_cast<size_t>(batch) * Hq), rows,
+                                                rows_kv, static_cast<int64_t>(batch) * Hkv);
+    if (!(sizeof(T) == 2 && D == 128 && rows >= FWD_WAVE_MIN_ROWS)) { pace = nullptr; even = nullptr; }
+    hipError_t e = launch_lpt_order(row_ptr, rows, N, col_cap, order, pace, even, s);
     if (e != hipSuccess) return e;
     if (o_lo) {
         if constexpr (sizeof(T) == 2) {
@@ -354,16 +370,17 @@ static hipError_t launch_fwd_t(const void* q, const void* k, const void* v, cons
             if (e != hipSuccess) return e;
         }
     }
-    if constexpr (sizeof(T) == 2) {
-        if (rows >= FWD_WAVE_MIN_ROWS)
-            return launch_attn_fwd_wave(D, q, k, v, row_ptr, col_idx, col_cap, o, lse, o_lo, order, pace, rows, Hq, Hkv, N, cg, fl, s);
+    if (even) {
+        e = launch_attn_fwd_wave(q, k, v, row_ptr, col_idx, col_cap, o, lse, o_lo, order, pace, even, rows, Hq, Hkv, N,
+                                 cg, fl, s);
+        if (e != hipSuccess) return e;
     }
     if (o_lo) {
-        if (cg.padded) launch_fwd_k<T, D, true, true>(q, k, v, row_ptr, col_idx, col_cap, o, lse, o_lo, order, rows, Hq, Hkv, N, cg, fl, s);
-        else launch_fwd_k<T, D, true, false>(q, k, v, row_ptr, col_idx, col_cap, o, lse, o_lo, order, rows, Hq, Hkv, N, cg, fl, s);
+        if (cg.padded) launch_fwd_k<T, D, true, true>(q, k, v, row_ptr, col_idx, col_cap, o, lse, o_lo, order, even, rows, Hq, Hkv, N, cg, fl, s);
+        else launch_fwd_k<T, D, true, false>(q, k, v, row_ptr, col_idx, col_cap, o, lse, o_lo, order, even, rows, Hq, Hkv, N, cg, fl, s);
     } else {
-        if (cg.padded) launch_fwd_k<T, D, false, true>(q, k, v, row_ptr, col_idx, col_cap, o, lse, nullptr, order, rows, Hq, Hkv, N, cg, fl, s);
-        else launch_fwd_k<T, D, false, false>(q, k, v, row_ptr, col_idx, col_cap, o, lse, nullptr, order, rows, Hq, Hkv, N, cg, fl, s);
+        if (cg.padded) launch_fwd_k<T, D, false, true>(q, k, v, row_ptr, col_idx, col_cap, o, lse, nullptr, order, even, rows, Hq, Hkv, N, cg, fl, s);
+        else launch_fwd_k<T, D, false, false>(q, k, v, row_ptr, col_idx, col_cap, o, lse, nullptr, order, even, rows, Hq, Hkv, N, cg, fl, s);
     }
     return hipGetLastError();
 }

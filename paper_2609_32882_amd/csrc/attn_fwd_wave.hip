@@ -1,4 +1,27 @@
-// Block-sparse attention forward for bf16, one wave per query block.
+// Block-sparse attention forward for bf16 and D = 128, one wave per query block
+// (VSA2 Sec. 2.1 with a block mask, Sec. 2.2 Eq. block_sparse).  attn_fwd.hip
+// states the computation and which launches and heads come here.
+//
+// What bounds the two-wave kernel at 720p (40 heads, top-120, 5.76M pairs, 189
+// GB of K/V gathers): its waves stall on each other's barriers and on LDS
+// reads, and 85 GB of the gathers miss the L2s, which pull at most about 7
+// TB/s.  Here:
+//  - One wave owns all 64 queries: every K and V^T fragment read from LDS feeds
+//    two MFMAs instead of one (half the LDS reads), and there are no barriers.
+//    Its 128 accumulators and 64 Q registers live in AGPRs (one wave per SIMD).
+//  - The wave is its own pipeline over half-tiles of 32 keys: while the softmax
+//    of half-tile i runs on the vector unit, the MFMAs compute S of half-tile
+//    i + 1 and P V of half-tile i - 1, one MFMA to one element (one exponential
+//    and about 3.5 other vector instructions) per slot.  Without memory (tiles
+//    left in LDS) this takes 7.6 ms at 720p, 1.6 PFLOP/s.
+//  - No row max per tile: p = 2^(s c - m) against a reference m that is raised
+//    (and the tile redone) only when the lane's sum of a tile passes 2^8.
+//  - Each half-tile's buffer is refilled as soon as its last fragment is read;
+//    three of the four are in flight.
+//  - Paced walks (wave_tile.hpp): the waves of an XCD stay within a few list
+//    entries of each other.  Unpaced, this kernel outruns the L2s: 139 GB of
+//    misses, 19.9 ms; paced 54 GB, 13.4 ms (14.9 ms for the two-wave kernel);
+//    with every gather an L2 hit 11.5 ms.
 #include <type_traits>
 
 #include "wave_tile.hpp"
@@ -17,14 +40,15 @@ __device__ __forceinline__ void for_each_ic(Fn&& fn) {
     }
 }
 
-template <int D, bool COMP, bool PAD>
+template <bool COMP, bool PAD>
 __global__ __launch_bounds__(64, 1) void attn_fwd_wave_kernel(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
     const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx, int64_t col_cap,
     bf16_t* __restrict__ o, float* __restrict__ lse, bf16_t* __restrict__ o_lo, int Hq, int Hkv, int N, float c_log2,
-    int period, const int32_t* __restrict__ order, uint32_t* __restrict__ pace, cube_grid grid,
-    block_flag_layout fl) {
+    int period, const int32_t* __restrict__ order, uint32_t* __restrict__ pace, const float* __restrict__ even,
+    cube_grid grid, block_flag_layout fl) {
     using F = frag_bf16;
+    constexpr int D = 128;
     constexpr int RB = 2 * D;
     constexpr int KS = D / 16, MT = D / 32;
     constexpr int ND = wave_copy<RB>::ND, HALF = wave_copy<RB>::HALF;
@@ -38,6 +62,8 @@ __global__ __launch_bounds__(64, 1) void attn_fwd_wave_kernel(
     const int lane = threadIdx.x, half = lane >> 5;
     const int64_t row = work_row(order, xcd_item(blockIdx.x, gridDim.x), gridDim.x);
     const int64_t bh = row / N;
+    const float avg = even[bh];              // this head's average list length
+    if (!(avg > 0.f)) return;                // uneven lists: a head of the two-wave kernel
     const int n = static_cast<int>(row % N);
     const int b = static_cast<int>(bh / Hq), h = static_cast<int>(bh % Hq);
     const int64_t kvh = static_cast<int64_t>(b) * Hkv + h / (Hq / Hkv);
@@ -76,11 +102,9 @@ __global__ __launch_bounds__(64, 1) void attn_fwd_wave_kernel(
             big = __any(hit);
         }
     }
-    // rows about as long as the head's average are paced: they start at the
-    // list's first entry; others start at the phase of their place in the launch
-    const int64_t h0 = row_ptr[bh * N], h1 = row_ptr[(bh + 1) * N];
-    const float avg = static_cast<float>(h1 - h0) / static_cast<float>(N);
-    const bool paced = __builtin_amdgcn_readfirstlane(cnt >= 8 && fabsf(cnt - avg) <= avg * (1.f / 16) ? 1 : 0) != 0;
+    // rows about as long as the head's average are paced, from their list's
+    // first entry; the others start at the phase of their place in the launch
+    const bool paced = __builtin_amdgcn_readfirstlane(fabsf(cnt - avg) <= avg * (1.f / 16) ? 1 : 0) != 0;
     pace_clock clk;
     clk.words = reinterpret_cast<uint64_t>(pace + xcc_id() * PACE_SLOTS);
     clk.copy = pace_lds;
@@ -417,35 +441,24 @@ __global__ __launch_bounds__(64, 1) void attn_fwd_wave_kernel(
     }
 }
 
-template <int D, bool COMP, bool PAD>
-static void launch_wave(const void* q, const void* k, const void* v, const int32_t* row_ptr, const int32_t* col_idx,
-                        int64_t col_cap, void* o, float* lse, void* o_lo, const int32_t* order, uint32_t* pace, int64_t rows,
-                        int Hq, int Hkv, int N, const cube_grid& cg, const block_flag_layout& fl, hipStream_t s) {
-    const float c = 1.4426950408889634f / sqrtf(static_cast<float>(D));
-    hipLaunchKernelGGL((attn_fwd_wave_kernel<D, COMP, PAD>), dim3(static_cast<unsigned>(rows)), dim3(64), 0, s,
-                       static_cast<const bf16_t*>(q), static_cast<const bf16_t*>(k), static_cast<const bf16_t*>(v),
-                       row_ptr, col_idx, col_cap, static_cast<bf16_t*>(o), lse, static_cast<bf16_t*>(o_lo), Hq, Hkv, N,
-                       c, resident_per_xcd<attn_fwd_wave_kernel<D, COMP, PAD>>(64), order, pace, cg, fl);
-}
-
-hipError_t launch_attn_fwd_wave(int D, const void* q, const void* k, const void* v, const int32_t* row_ptr,
+hipError_t launch_attn_fwd_wave(const void* q, const void* k, const void* v, const int32_t* row_ptr,
                                 const int32_t* col_idx, int64_t col_cap, void* o, float* lse, void* o_lo,
-                                const int32_t* order, uint32_t* pace, int64_t rows, int Hq, int Hkv, int N,
-                                const cube_grid& cg, const block_flag_layout& fl, hipStream_t s) {
-    auto go = [&](auto d, auto comp, auto pad) {
-        launch_wave<decltype(d)::value, decltype(comp)::value, decltype(pad)::value>(
-            q, k, v, row_ptr, col_idx, col_cap, o, lse, o_lo, order, pace, rows, Hq, Hkv, N, cg, fl, s);
+                                const int32_t* order, uint32_t* pace, const float* even, int64_t rows, int Hq,
+                                int Hkv, int N, const cube_grid& cg, const block_flag_layout& fl, hipStream_t s) {
+    const float c = 1.4426950408889634f / sqrtf(128.f);
+    auto go = [&](auto comp, auto pad) {
+        constexpr bool COMP = decltype(comp)::value, PAD = decltype(pad)::value;
+        hipLaunchKernelGGL((attn_fwd_wave_kernel<COMP, PAD>), dim3(static_cast<unsigned>(rows)), dim3(64), 0, s,
+                           static_cast<const bf16_t*>(q), static_cast<const bf16_t*>(k),
+                           static_cast<const bf16_t*>(v), row_ptr, col_idx, col_cap, static_cast<bf16_t*>(o), lse,
+                           static_cast<bf16_t*>(o_lo), Hq, Hkv, N, c,
+                           resident_per_xcd<attn_fwd_wave_kernel<COMP, PAD>>(64), order, pace, even, cg, fl);
     };
-    auto with_d = [&](auto d) {
-        if (o_lo) {
-            if (cg.padded) go(d, std::true_type{}, std::true_type{}); else go(d, std::true_type{}, std::false_type{});
-        } else {
-            if (cg.padded) go(d, std::false_type{}, std::true_type{}); else go(d, std::false_type{}, std::false_type{});
-        }
-    };
-    if (D == 64) with_d(ic<64>{});
-    else if (D == 128) with_d(ic<128>{});
-    else return hipErrorInvalidValue;
+    if (o_lo) {
+        if (cg.padded) go(std::true_type{}, std::true_type{}); else go(std::true_type{}, std::false_type{});
+    } else {
+        if (cg.padded) go(std::false_type{}, std::true_type{}); else go(std::false_type{}, std::false_type{});
+    }
     return hipGetLastError();
 }
 

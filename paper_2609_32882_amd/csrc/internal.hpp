@@ -98,10 +98,12 @@ size_t bwd_ws_csr_order_offset(int batch, int Hq, int N);
 size_t bwd_ws_csc_order_offset(int batch, int Hq, int N);
 // Longest-first work order of the rows of ptr within each piece of a head
 // (n_per_head rows) that falls into one XCD range.
-// pace (may be null): the pacing counters, cleared for the launch that follows.
+// pace (may be null): the pacing words of the launch that follows, cleared; even:
+// per head, the average list length when its lists are even, else 0.
 constexpr size_t PACE_BYTES = 8192;
+constexpr float EVEN_MIN_LEN = 16.f;
 hipError_t launch_lpt_order(const int32_t* ptr, int64_t nrows, int64_t n_per_head, int64_t cap, int32_t* order,
-                            uint32_t* pace, hipStream_t s);
+                            uint32_t* pace, float* even, hipStream_t s);
 // Magnitude flags of the 64-token blocks of bf16 Q, K, V: q[row] for the
 // query blocks, kv[row] for the key blocks (K and V combined), 1 when a real
 // token holds a value above 7 in magnitude; any_q[g] / any_kv[g] per KV group
@@ -123,11 +125,12 @@ struct block_flag_layout {
 // two-term dS: dS = P (dP - Delta) is then a small difference of large
 // terms whose one-term rounding the gradients amplify.
 constexpr float DELTA_FLAG = 16.0f;
-// The bf16 forward with one wave per query block (attn_fwd_wave.hip).
-hipError_t launch_attn_fwd_wave(int D, const void* q, const void* k, const void* v, const int32_t* row_ptr,
+// The bf16 forward with one wave per query block (attn_fwd_wave.hip), for the
+// heads that `even` marks.
+hipError_t launch_attn_fwd_wave(const void* q, const void* k, const void* v, const int32_t* row_ptr,
                                 const int32_t* col_idx, int64_t col_cap, void* o, float* lse, void* o_lo,
-                                const int32_t* order, uint32_t* pace, int64_t rows, int Hq, int Hkv, int N,
-                                const cube_grid& cg, const block_flag_layout& fl, hipStream_t s);
+                                const int32_t* order, uint32_t* pace, const float* even, int64_t rows, int Hq,
+                                int Hkv, int N, const cube_grid& cg, const block_flag_layout& fl, hipStream_t s);
 block_flag_layout block_flags_at(void* base, int64_t rows_q, int64_t rows_kv, int64_t groups);
 size_t block_flags_bytes(int64_t rows_q, int64_t rows_kv, int64_t groups);
 hipError_t launch_block_flags(const void* q, const void* k, const void* v, const block_flag_layout& f, int64_t rows_q,

@@ -107,14 +107,41 @@ __device__ void lpt_segment(const int32_t* __restrict__ ptr, int64_t cap, int32_
 __global__ __launch_bounds__(PLAN_NT) void lpt_order_kernel(const int32_t* __restrict__ ptr, int64_t nrows,
                                                             int64_t n_per_head, int64_t cap,
                                                             int32_t* __restrict__ order,
-                                                            uint32_t* __restrict__ pace) {
-    if (pace && blockIdx.x == 0)
-        for (int i = threadIdx.x; i < static_cast<int>(PACE_BYTES / 4); i += PLAN_NT) pace[i] = 0u;
+                                                            uint32_t* __restrict__ pace,
+                                                            float* __restrict__ even) {
     __shared__ uint32_t hist[PLAN_CLASSES][PLAN_NT];
     __shared__ uint32_t part[PLAN_NT];
     __shared__ int64_t red[PLAN_NT / 64];
     const int64_t h0 = static_cast<int64_t>(blockIdx.x) * n_per_head;
     const int64_t h1 = h0 + n_per_head < nrows ? h0 + n_per_head : nrows;
+    if (pace) {
+        // clears the pacing words of the launch that follows, and says whether
+        // this head's lists are even: at least EVEN_MIN_LEN entries on average,
+        // 7 of 8 rows within 1/16 of the average (then the average, else 0)
+        if (blockIdx.x == 0)
+            for (int i = threadIdx.x; i < static_cast<int>(PACE_BYTES / 4); i += PLAN_NT) pace[i] = 0u;
+        __shared__ int64_t sums[PLAN_NT / 64];
+        int64_t mine = 0;
+        for (int64_t i = h0 + threadIdx.x; i < h1; i += PLAN_NT) mine += row_len(ptr, i, cap);
+        for (int off = 32; off >= 1; off >>= 1) mine += __shfl_xor(mine, off, 64);
+        if ((threadIdx.x & 63) == 0) sums[threadIdx.x >> 6] = mine;
+        __syncthreads();
+        int64_t total = 0;
+#pragma unroll
+        for (int w = 0; w < PLAN_NT / 64; ++w) total += sums[w];
+        const float avg = static_cast<float>(total) / static_cast<float>(h1 - h0);
+        __syncthreads();
+        mine = 0;
+        for (int64_t i = h0 + threadIdx.x; i < h1; i += PLAN_NT)
+            mine += fabsf(static_cast<float>(row_len(ptr, i, cap)) - avg) <= avg * (1.f / 16) ? 1 : 0;
+        for (int off = 32; off >= 1; off >>= 1) mine += __shfl_xor(mine, off, 64);
+        if ((threadIdx.x & 63) == 0) sums[threadIdx.x >> 6] = mine;
+        __syncthreads();
+        int64_t near = 0;
+#pragma unroll
+        for (int w = 0; w < PLAN_NT / 64; ++w) near += sums[w];
+        if (threadIdx.x == 0) even[blockIdx.x] = avg >= EVEN_MIN_LEN && 8 * near >= 7 * (h1 - h0) ? avg : 0.f;
+    }
     const int64_t q = nrows >> 3, r = nrows & 7;
     int64_t s0 = h0;
     while (s0 < h1) {
@@ -131,11 +158,11 @@ __global__ __launch_bounds__(PLAN_NT) void lpt_order_kernel(const int32_t* __res
 }
 
 hipError_t launch_lpt_order(const int32_t* ptr, int64_t nrows, int64_t n_per_head, int64_t cap, int32_t* order,
-                            uint32_t* pace, hipStream_t s) {
+                            uint32_t* pace, float* even, hipStream_t s) {
     if (nrows <= 0) return hipSuccess;
     const int64_t heads = (nrows + n_per_head - 1) / n_per_head;
     hipLaunchKernelGGL(lpt_order_kernel, dim3(static_cast<unsigned>(heads)), dim3(PLAN_NT), 0, s, ptr, nrows,
-                       n_per_head, cap, order, pace);
+                       n_per_head, cap, order, pace, even);
     return hipGetLastError();
 }
 

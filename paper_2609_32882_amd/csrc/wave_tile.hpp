@@ -1,19 +1,17 @@
-// Building blocks of the one-wave attention kernels (attn_fwd_wave.hip,
-// dq_wave.hip): 64-row bf16 tiles in unpadded, XOR-swizzled LDS rows, their
+// Building blocks of the one-wave attention kernel (attn_fwd_wave.hip): 64-row bf16 tiles in unpadded, XOR-swizzled LDS rows, their
 // asynchronous copies and their fragment reads.
 //
 // A tile is two half-tiles of 32 rows.  Tile row y lies at LDS row y; the
 // 16-byte chunk c of a row lies at chunk c ^ wt_swizzle(y).  64 banks of 4
-// bytes are 16 chunks, so with 256-byte rows (D = 128) the bank of a piece
-// is its physical chunk, with 128-byte rows (D = 64) its chunk plus 8 for
-// odd rows.
+// bytes are 16 chunks, so with 256-byte rows (D = 128) the bank of a piece is
+// its physical chunk.
 //  - A row read (wt_row_frag, ds_read_b128) serves 16 lanes per clock, which
 //    read one chunk c of the 16 rows of a 16-row block: the swizzle gives
 //    those rows 16 different bank groups.
 //  - A transposing read (wt_col_frag, ds_read_b64_tr_b16) serves a half-wave
 //    per clock: 4 consecutive chunks (an aligned group) of 4 consecutive rows.
-//    The high two bits of the swizzle (D = 64: its high bit and the row's
-//    parity) differ among those rows, so the groups fall on disjoint banks.
+//    The high two bits of the swizzle differ among those rows, so the groups
+//    fall on disjoint banks.
 // No padding and no row permutation: a half-tile is a whole number of 1 KB
 // copies, every fourth of which has the same per-lane source offset (the
 // swizzle repeats after 16 rows), so four offset registers serve all tiles.
@@ -25,7 +23,8 @@ namespace vsa2 {
 
 template <int RB>
 __host__ __device__ constexpr int wt_swizzle(int y) {
-    return RB == 256 ? ((y & 3) << 2) | ((y >> 2) & 3) : (((y >> 1) & 1) << 2) | ((y >> 2) & 3);
+    static_assert(RB == 256, "row bytes");
+    return ((y & 3) << 2) | ((y >> 2) & 3);
 }
 
 // Asynchronous copies of half-tiles of 32 rows of RB bytes by one wave.
@@ -33,7 +32,6 @@ template <int RB>
 struct wave_copy {
     static constexpr int HALF = 32 * RB;          // bytes of a half-tile
     static constexpr int ND = HALF / 1024;        // copies per half-tile
-    static_assert(RB == 128 || RB == 256, "row bytes");
     int off[4];                                   // copy j: source offset off[j % 4] + 1024 j
 
     __device__ __forceinline__ explicit wave_copy(int lane) {
