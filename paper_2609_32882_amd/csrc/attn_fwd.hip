@@ -55,9 +55,10 @@ __global__ __launch_bounds__(AF_NT, 2) void attn_fwd_kernel(
     __shared__ __align__(1024) char v_lds[VT::BYTES];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = wave_id(), half = lane >> 5;
-    const int64_t row = work_row(order, xcd_item(blockIdx.x, gridDim.x), gridDim.x);
-    const int64_t bh = row / N;
+    const int64_t item = xcd_item(blockIdx.x, gridDim.x);
+    const int64_t bh = item / N;             // the order permutes rows within a head
     if (even && even[bh] > 0.f) return;      // a head of the one-wave kernel
+    const int64_t row = work_row(order, item, gridDim.x);
     const int n = static_cast<int>(row % N);
     const int b = static_cast<int>(bh / Hq), h = static_cast<int>(bh % Hq);
     const int hkv = h / (Hq / Hkv);
@@ -361,7 +362,8 @@ static hipError_t launch_fwd_t(const void* q, const void* k, const void* v, cons
     float* even = reinterpret_cast<float*>(at + PACE_BYTES);
     const block_flag_layout fl = block_flags_at(at + PACE_BYTES + align256f(4 * static_cast<size_t>(batch) * Hq), rows,
                                                 rows_kv, static_cast<int64_t>(batch) * Hkv);
-    if (!(sizeof(T) == 2 && D == 128 && rows >= FWD_WAVE_MIN_ROWS)) { pace = nullptr; even = nullptr; }
+    if (!(sizeof(T) == 2 && D == 128 && rows >= FWD_WAVE_MIN_ROWS &&
+          static_cast<float>(col_cap) >= EVEN_MIN_LEN * static_cast<float>(rows))) { pace = nullptr; even = nullptr; }
     hipError_t e = launch_lpt_order(row_ptr, rows, N, col_cap, order, pace, even, s);
     if (e != hipSuccess) return e;
     if (o_lo) {

@@ -60,10 +60,11 @@ __global__ __launch_bounds__(64, 1) void attn_fwd_wave_kernel(
     const char* v_lds = lds + 2 * HALF;
 
     const int lane = threadIdx.x, half = lane >> 5;
-    const int64_t row = work_row(order, xcd_item(blockIdx.x, gridDim.x), gridDim.x);
-    const int64_t bh = row / N;
+    const int64_t item = xcd_item(blockIdx.x, gridDim.x);
+    const int64_t bh = item / N;             // the order permutes rows within a head
     const float avg = even[bh];              // this head's average list length
     if (!(avg > 0.f)) return;                // uneven lists: a head of the two-wave kernel
+    const int64_t row = work_row(order, item, gridDim.x);
     const int n = static_cast<int>(row % N);
     const int b = static_cast<int>(bh / Hq), h = static_cast<int>(bh % Hq);
     const int64_t kvh = static_cast<int64_t>(b) * Hkv + h / (Hq / Hkv);
