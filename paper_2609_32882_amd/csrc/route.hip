@@ -658,22 +658,35 @@ __global__ __launch_bounds__(SEQ_NT) void seq_hist_kernel(const float* __restric
     if (sum) atomicAdd(&ghist[seq * 256 + tid], sum);
 }
 
-// One thread per sequence: the digit holding the target rank; clears the
-// histogram for the next pass.  After the last pass prefix = tau's bits and
-// rem = the number of entries equal to tau that are kept.
-__global__ void seq_pick_kernel(seq_state* __restrict__ st, uint32_t* __restrict__ ghist, int64_t nseq) {
-    const int64_t seq = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (seq >= nseq) return;
-    uint32_t* h = ghist + seq * 256;
-    int64_t r = st[seq].rem;
-    int d = 255;
-    for (; d > 0; --d) {
-        if (static_cast<int64_t>(h[d]) >= r) break;
-        r -= h[d];
+// One wave per sequence: the digit holding the target rank (the highest one
+// whose bin and the bins above hold at least rem entries); clears the histogram
+// for the next pass.  After the last pass prefix = tau's bits and rem = the
+// number of entries equal to tau that are kept.  Lane l holds bins 255 - 4l
+// down to 252 - 4l, so a prefix sum over lanes counts from the top.  (One
+// thread per sequence, walking its 256 bins: 23 us a pass.)
+__global__ __launch_bounds__(64) void seq_pick_kernel(seq_state* __restrict__ st, uint32_t* __restrict__ ghist) {
+    const int64_t seq = blockIdx.x;
+    const int lane = threadIdx.x;
+    uint4* h = reinterpret_cast<uint4*>(ghist + seq * 256) + (63 - lane);
+    const uint4 v = *h;
+    const uint32_t bin[4] = {v.w, v.z, v.y, v.x};       // descending digits
+    const uint32_t sum = bin[0] + bin[1] + bin[2] + bin[3];
+    uint32_t incl = sum;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t y = __shfl_up(incl, off, 64);
+        if (lane >= off) incl += y;
     }
-    st[seq].prefix = (st[seq].prefix << 8) | static_cast<uint32_t>(d);
-    st[seq].rem = static_cast<int32_t>(r);
-    for (int b = 0; b < 256; ++b) h[b] = 0;
+    const uint32_t r = static_cast<uint32_t>(st[seq].rem);
+    const uint64_t reach = __ballot(incl >= r);
+    const int src = reach ? __ffsll(static_cast<unsigned long long>(reach)) - 1 : 63;
+    *h = make_uint4(0u, 0u, 0u, 0u);
+    if (lane != src) return;
+    uint32_t left = r - (incl - sum);                   // rank within this lane's bins
+    int i = 0;
+    while (i < 3 && bin[i] < left) left -= bin[i++];
+    st[seq].prefix = (st[seq].prefix << 8) | static_cast<uint32_t>(255 - 4 * lane - i);
+    st[seq].rem = static_cast<int32_t>(left);
 }
 
 // One wave per row (N <= 64*PER).  PHASE 0: gt[row], eq[row].  PHASE 1:
@@ -829,8 +842,7 @@ hipError_t launch_select_seq(const float* scores, int64_t nseq, int N, int k, vo
     for (int pass = 0; pass < 4; ++pass) {
         hipLaunchKernelGGL(seq_hist_kernel, hgrid, dim3(SEQ_NT), 0, s, scores, nn, st, ghist, pass);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        hipLaunchKernelGGL(seq_pick_kernel, dim3(static_cast<unsigned>((nseq + 63) / 64)), dim3(64), 0, s, st,
-                           ghist, nseq);
+        hipLaunchKernelGGL(seq_pick_kernel, dim3(static_cast<unsigned>(nseq)), dim3(64), 0, s, st, ghist);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     if ((e = launch_seq_rows_any(0, scores, nrows, N, st, gt, eq, nullptr, nullptr, nullptr, 0, s)) != hipSuccess)
@@ -976,29 +988,48 @@ __global__ __launch_bounds__(CSC_NT) void csc_mark_lds_kernel(const int32_t* __r
     for (int i = threadIdx.x; i < N; i += CSC_NT) out[static_cast<int64_t>(i) * words] = marks[i];
 }
 
-__global__ void csc_count_kernel(const uint32_t* __restrict__ mask, int64_t nkrows, int words,
-                                 int32_t* __restrict__ counts) {
-    const int64_t r = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+// Entries of each key-block row: one wave per row, its mask words read 64 at a
+// time.  (One thread per row walked its words alone: with grouped heads a row
+// has hundreds of words and there are few rows.  4,800 rows of 375 words: count
+// 105 us, lists 198 us that way; 2,880 rows of 225 words: 63 and 172 us.)
+__global__ __launch_bounds__(256) void csc_count_kernel(const uint32_t* __restrict__ mask, int64_t nkrows, int words,
+                                                        int32_t* __restrict__ counts) {
+    const int lane = threadIdx.x & 63;
+    const int64_t r = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
     if (r >= nkrows) return;
     int c = 0;
-    for (int w = 0; w < words; ++w) c += __popc(mask[r * words + w]);
-    counts[r] = c;
+    for (int w = lane; w < words; w += 64) c += __popc(mask[r * words + w]);
+    c = wave_sum_i(c);
+    if (lane == 0) counts[r] = c;
 }
 
-__global__ void csc_emit_kernel(const uint32_t* __restrict__ mask, int64_t nkrows, int words,
-                                const int32_t* __restrict__ kv_ptr, int32_t* __restrict__ kv_idx,
-                                int64_t col_cap) {
-    const int64_t r = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+// The lists: a wave prefix sum over 64 words' populations gives each lane the
+// place of its word's entries.
+__global__ __launch_bounds__(256) void csc_emit_kernel(const uint32_t* __restrict__ mask, int64_t nkrows, int words,
+                                                       const int32_t* __restrict__ kv_ptr,
+                                                       int32_t* __restrict__ kv_idx, int64_t col_cap) {
+    const int lane = threadIdx.x & 63;
+    const int64_t r = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
     if (r >= nkrows) return;
     int64_t pos = kv_ptr[r];
-    for (int w = 0; w < words; ++w) {
-        uint32_t m = mask[r * words + w];
+    for (int w0 = 0; w0 < words; w0 += 64) {
+        const int w = w0 + lane;
+        uint32_t m = w < words ? mask[r * words + w] : 0u;
+        const int n = __popc(m);
+        int incl = n;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int y = __shfl_up(incl, off, 64);
+            if (lane >= off) incl += y;
+        }
+        int64_t at = pos + incl - n;
         while (m) {
             const int bit = __ffs(m) - 1;
             m &= m - 1;
-            if (pos < col_cap) kv_idx[pos] = w * 32 + bit;
-            ++pos;
+            if (at < col_cap) kv_idx[at] = w * 32 + bit;
+            ++at;
         }
+        pos += __shfl(incl, 63, 64);
     }
 }
 
@@ -1019,11 +1050,11 @@ hipError_t launch_csc(const int32_t* row_ptr, const int32_t* col_idx, int batch,
                            row_ptr, col_idx, nrows, N, Hq, Hkv, words, col_cap, mask);
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(csc_count_kernel, dim3(static_cast<unsigned>((nkrows + 255) / 256)), dim3(256), 0, s,
+    hipLaunchKernelGGL(csc_count_kernel, dim3(static_cast<unsigned>((nkrows + 3) / 4)), dim3(256), 0, s,
                        mask, nkrows, words, kv_counts);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if ((e = launch_scan(kv_counts, nkrows, kv_ptr, s)) != hipSuccess) return e;
-    hipLaunchKernelGGL(csc_emit_kernel, dim3(static_cast<unsigned>((nkrows + 255) / 256)), dim3(256), 0, s,
+    hipLaunchKernelGGL(csc_emit_kernel, dim3(static_cast<unsigned>((nkrows + 3) / 4)), dim3(256), 0, s,
                        mask, nkrows, words, kv_ptr, kv_idx, col_cap);
     return hipGetLastError();
 }
