@@ -85,7 +85,7 @@ int64_t keep_per_row(const vsa2_select* sel, int64_t N) {
 }
 
 struct route_ws {
-    size_t lse2, scores, counts, mask, kv_counts, seq, total;
+    size_t lse2, scores, counts, mask, kv_counts, seq, rules, total;
 };
 
 route_ws route_layout(const vsa2_problem* p, const shape& s, const vsa2_select* sel) {
@@ -100,6 +100,8 @@ route_ws route_layout(const vsa2_problem* p, const shape& s, const vsa2_select* 
     w.seq = at;
     if (sel->mode == VSA2_SEL_SEQ_TOPK)
         at = align_up(at + vsa2::seq_workspace_bytes(static_cast<int64_t>(p->batch) * p->heads_q, s.rows_q));
+    w.rules = at;
+    if (sel->mode == VSA2_SEL_MASS) at = align_up(at + 8 * static_cast<size_t>(s.rows_q));
     w.total = at;
     return w;
 }
@@ -217,11 +219,12 @@ vsa2_status vsa2_route(const vsa2_problem* p, const vsa2_select* sel, const void
             VSA2_TRY_HIP(vsa2::launch_uniform_ptr(row_ptr, s.rows_q, static_cast<int>(keep), stream));
         } else {
             VSA2_TRY_HIP(vsa2::launch_select(0, scores, s.rows_q, N, sel->mode, sel->k, sel->mass, sel->cap,
-                                             counts, nullptr, nullptr, col_cap, stream));
+                                             counts, base + w.rules, nullptr, nullptr, col_cap, stream));
             VSA2_TRY_HIP(vsa2::launch_scan(counts, s.rows_q, row_ptr, stream));
         }
         VSA2_TRY_HIP(vsa2::launch_select(1, scores, s.rows_q, N, sel->mode, sel->k, sel->mass, sel->cap,
-                                         counts, row_ptr, col_idx, col_cap, stream));
+                                         counts, sel->mode == VSA2_SEL_MASS ? base + w.rules : nullptr, row_ptr,
+                                         col_idx, col_cap, stream));
     }
     if (kv_ptr) {
         VSA2_TRY_HIP(vsa2::launch_csc(row_ptr, col_idx, p->batch, p->heads_q, p->heads_kv, N, col_cap,

@@ -66,8 +66,10 @@ hipError_t launch_pool(int dtype, const void* x, void* out, int64_t nbh, int N, 
 hipError_t launch_route_passes(int dtype, int D, int G, const void* qr, const void* kr, float* lse2,
                                float* scores, int batch, int Hq, int Hkv, int N, const cube_grid& cg, int Rt,
                                int Rh, int Rw, hipStream_t s);
+// Phase 0: counts and rules (8 bytes per row); phase 1: the indices, by the
+// rules phase 0 stored or (rules null) decided again.
 hipError_t launch_select(int phase, const float* scores, int64_t nrows, int N, int mode, int k,
-                         float mass, int cap, int32_t* counts, const int32_t* row_ptr,
+                         float mass, int cap, int32_t* counts, void* rules, const int32_t* row_ptr,
                          int32_t* col_idx, int64_t col_cap, hipStream_t s);
 hipError_t launch_scan(const int32_t* counts, int64_t n, int32_t* ptr, hipStream_t s);
 // Sequence-level top-(N k) selection over nseq maps of N x N scores.
