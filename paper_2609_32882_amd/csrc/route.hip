@@ -22,26 +22,32 @@ namespace vsa2 {
 // sequence of Lj tokens: the N*B video tokens, then any text tokens): all
 // Pt*Ph*Pw of them unless the grid is padded, where the real tokens of a
 // sub-cube form a box and an all-padding sub-cube pools to 0.
-// FP = 2: sub-cubes of 2 x 2 x 2 tokens (the router's pool), the eight
-// loads unrolled and issued together; FP = 0: any sub-cube (runtime loops).
-template <typename T, int FP>
+// FP = 2, 4: sub-cubes of 2 x 2 x 2 (the router's pool) or 4 x 4 x 4 tokens
+// (the whole cube: the coarse branch, VSA's router), their 8 (16 a layer) loads
+// unrolled and issued together; FP = 0: any sub-cube (runtime loops).
+// HBM-bound; I is the index type (64-bit divisions by N and G cost as much as
+// the sums, so launches below 2^31 threads take 32-bit ones).  786 MB pooled:
+// as whole cubes 167 -> 151 us, as 2 x 2 x 2 sub-cubes 180 -> 172 us.
+template <typename T, int FP, typename I>
 __global__ __launch_bounds__(256) void pool_kernel(const T* __restrict__ x, T* __restrict__ out,
                                                    int64_t nthreads, int N, int64_t Lj, int D, int G, int Gh,
                                                    int Gw, int Pt, int Ph, int Pw, int B, cube_grid grid) {
-    const int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (t >= nthreads) return;
-    const int chunks = D / 8;
+    const I t = static_cast<I>(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (t >= static_cast<I>(nthreads)) return;
+    const I chunks = D / 8;
     const int ch = static_cast<int>(t % chunks);
-    const int64_t orow = t / chunks;                  // (bh*N + n)*G + g
-    const int g = static_cast<int>(orow % G);
-    const int64_t cube = orow / G;                   // bh*N + n
+    const I orow = t / chunks;                        // (bh*N + n)*G + g
+    const I cube = orow / static_cast<I>(G);         // bh*N + n
+    const int g = static_cast<int>(orow - cube * static_cast<I>(G));
+    const I bh = cube / static_cast<I>(N);
+    const int nc = static_cast<int>(cube - bh * static_cast<I>(N));
     const int gt = g / (Gh * Gw), gh = (g / Gw) % Gh, gw = g % Gw;
     const int Bh = grid.Bh, Bw = grid.Bw;
-    const T* xc = x + ((cube / N) * Lj + (cube % N) * B) * D;   // the cube's first token
+    const T* xc = x + (static_cast<int64_t>(bh) * Lj + static_cast<int64_t>(nc) * B) * D;   // the cube's first token
     // real part of the sub-cube: [0, et) x [0, eh) x [0, ew) of its offsets
     int et = Pt, eh = Ph, ew = Pw;
     if (grid.padded) {
-        const int3 e = cube_extent(grid, static_cast<int>(cube % N));
+        const int3 e = cube_extent(grid, nc);
         et = max(0, min(Pt, e.x - gt * Pt));
         eh = max(0, min(Ph, e.y - gh * Ph));
         ew = max(0, min(Pw, e.z - gw * Pw));
@@ -76,8 +82,8 @@ __global__ __launch_bounds__(256) void pool_kernel(const T* __restrict__ x, T* _
     if constexpr (FP > 0) {
         // fixed bounds, no branch: for a token outside the real part of a
         // cut sub-cube the sub-cube's first token is read (it exists in
-        // memory) and not added, so the eight loads issue together
-#pragma unroll
+        // memory) and not added, so the loads issue together
+#pragma unroll FP == 2 ? 2 : 1
         for (int rt = 0; rt < FP; ++rt)
 #pragma unroll
             for (int rh = 0; rh < FP; ++rh)
@@ -93,7 +99,7 @@ __global__ __launch_bounds__(256) void pool_kernel(const T* __restrict__ x, T* _
     }
     const int cnt = et * eh * ew;
     const double P = static_cast<double>(cnt > 0 ? cnt : 1);
-    T* dst = out + orow * D + ch * 8;
+    T* dst = out + static_cast<int64_t>(orow) * D + ch * 8;
     if constexpr (sizeof(T) == 2) {
         uint32_t u[4];
 #pragma unroll
@@ -118,17 +124,23 @@ hipError_t launch_pool(int dtype, const void* x, void* out, int64_t nbh, int N, 
     if (nthreads == 0) return hipSuccess;
     const int64_t blocks = (nthreads + 255) / 256;
     const int B = Bt * Bh * Bw;
-    auto go = [&](auto elem, auto fixed) {
+    auto go = [&](auto elem, auto fixed, auto index) {
         using E = decltype(elem);
-        hipLaunchKernelGGL((pool_kernel<E, decltype(fixed)::value>), dim3(blocks), dim3(256), 0, s,
+        hipLaunchKernelGGL((pool_kernel<E, decltype(fixed)::value, decltype(index)>), dim3(blocks), dim3(256), 0, s,
                            static_cast<const E*>(x), static_cast<E*>(out), nthreads, N, Lj, D, G, Gh, Gw, Pt, Ph,
                            Pw, B, grid);
     };
-    const bool two = Pt == 2 && Ph == 2 && Pw == 2;
+    auto with = [&](auto elem, auto index) {
+        if (Pt == 2 && Ph == 2 && Pw == 2) go(elem, std::integral_constant<int, 2>{}, index);
+        else if (Pt == 4 && Ph == 4 && Pw == 4) go(elem, std::integral_constant<int, 4>{}, index);
+        else go(elem, std::integral_constant<int, 0>{}, index);
+    };
+    // the last block's threads past nthreads must not wrap either
+    const bool narrow = nthreads < (int64_t(1) << 31);
     if (dtype == 1) {
-        if (two) go(bf16_t{}, std::integral_constant<int, 2>{}); else go(bf16_t{}, std::integral_constant<int, 0>{});
+        if (narrow) with(bf16_t{}, uint32_t{}); else with(bf16_t{}, uint64_t{});
     } else {
-        if (two) go(0.f, std::integral_constant<int, 2>{}); else go(0.f, std::integral_constant<int, 0>{});
+        if (narrow) with(0.f, uint32_t{}); else with(0.f, uint64_t{});
     }
     return hipGetLastError();
 }
