@@ -19,21 +19,38 @@ namespace vsa2 {
 constexpr int CB_NT = 128;   // two waves, 32 rows each
 constexpr float kLog2eC = 1.4426950408889634f;
 
-// Rows row0 .. row0+63 of a [rows][D] tensor into a padded LDS tile, LDS row r
-// holding global row row0 + tile_row_at(r) (bf16: column groups in the
-// cgroup_pos order the fragment readers expect); rows >= nrows are zero.
+// Rows row0 .. row0+63 of a [rows][D] tensor on their way into a padded LDS
+// tile, LDS row r holding global row row0 + tile_row_at(r) (bf16: column groups
+// in the cgroup_pos order the fragment readers expect); rows >= nrows are zero.
+// bf16 tiles are read one tile ahead into registers (fetch), so the reads are in
+// flight during the products of the tile before; fp32 ones, twice the size, are
+// read where they are stored.  The grid is at most one round of workgroups
+// (760 at 720p), so nothing else hides them.
 template <int RB, bool CPERM>
-__device__ __forceinline__ void load_rows_sync(char* lds, const char* g, int64_t row0, int64_t nrows, int tid) {
-    constexpr int CH = RB / 16;
-    for (int c = tid; c < 64 * CH; c += CB_NT) {
-        const int r = c / CH, ch = c % CH;
-        const int64_t gr = row0 + tile_row_at<RB>(r);
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (gr < nrows) v = *reinterpret_cast<const uint4*>(g + gr * RB + ch * 16);
-        const int pc = CPERM ? cgroup_pos<RB>(ch >> 1) * 32 + (ch & 1) * 16 : ch * 16;
-        *reinterpret_cast<uint4*>(lds + r * (RB + 16) + pc) = v;
+struct row_stage {
+    static constexpr int CH = RB / 16, PER = 64 * CH / CB_NT;
+    static constexpr bool AHEAD = CPERM;
+    uint4 v[AHEAD ? PER : 1];
+
+    static __device__ __forceinline__ uint4 read(const char* g, int64_t row0, int64_t nrows, int c) {
+        const int64_t gr = row0 + tile_row_at<RB>(c / CH);
+        return gr < nrows ? *reinterpret_cast<const uint4*>(g + gr * RB + (c % CH) * 16) : make_uint4(0, 0, 0, 0);
     }
-}
+    __device__ __forceinline__ void fetch(const char* g, int64_t row0, int64_t nrows, int tid) {
+        if constexpr (AHEAD) {
+#pragma unroll
+            for (int i = 0; i < PER; ++i) v[i] = read(g, row0, nrows, tid + i * CB_NT);
+        }
+    }
+    __device__ __forceinline__ void store(char* lds, const char* g, int64_t row0, int64_t nrows, int tid) const {
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int c = tid + i * CB_NT, r = c / CH, ch = c % CH;
+            const int pc = CPERM ? cgroup_pos<RB>(ch >> 1) * 32 + (ch & 1) * 16 : ch * 16;
+            *reinterpret_cast<uint4*>(lds + r * (RB + 16) + pc) = AHEAD ? v[AHEAD ? i : 0] : read(g, row0, nrows, c);
+        }
+    }
+};
 
 template <typename F>
 __device__ __forceinline__ void zero_frag(F& f) {
@@ -88,22 +105,33 @@ __global__ __launch_bounds__(CB_NT) void coarse_fwd_kernel(const T* __restrict__
     const char* kb = reinterpret_cast<const char*>(kc + kv * N * D);
     const char* vb = reinterpret_cast<const char*>(vc + kv * N * D);
     const int ntiles = (N + 63) / 64;
+    row_stage<RB, E == 2> ks_, vs_;
+    ks_.fetch(kb, 0, N, tid);
+    vs_.fetch(vb, 0, N, tid);
     for (int kt = 0; kt < ntiles; ++kt) {
         __syncthreads();                  // previous tile's readers are done
-        load_rows_sync<RB, E == 2>(k_lds, kb, static_cast<int64_t>(kt) * 64, N, tid);
-        load_rows_sync<RB, E == 2>(v_lds, vb, static_cast<int64_t>(kt) * 64, N, tid);
+        ks_.store(k_lds, kb, static_cast<int64_t>(kt) * 64, N, tid);
+        vs_.store(v_lds, vb, static_cast<int64_t>(kt) * 64, N, tid);
         __syncthreads();
+        if (kt + 1 < ntiles) {
+            ks_.fetch(kb, static_cast<int64_t>(kt + 1) * 64, N, tid);
+            vs_.fetch(vb, static_cast<int64_t>(kt + 1) * 64, N, tid);
+        }
+        // fragments of a product are requested together (fp32: one by one),
+        // the other accumulator's products in between
         f32x16_t s[2];
 #pragma unroll
-        for (int t2 = 0; t2 < 2; ++t2) {
+        for (int t2 = 0; t2 < 2; ++t2)
 #pragma unroll
             for (int i = 0; i < 16; ++i) s[t2][i] = 0.f;
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                F a;
-                lds_frag_s<RB>(a, k_lds, t2 * 32 + (lane & 31), ks * 16 + half * 8);
-                mma(s[t2], a, qf[ks]);
-            }
+        for (int k2 = 0; k2 < KS; k2 += 2) {
+            F a[2][2];
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+                lds_frag_s<RB>(a[x & 1][x >> 1], k_lds, (x & 1) * 32 + (lane & 31), (k2 + (x >> 1)) * 16 + half * 8);
+#pragma unroll
+            for (int x = 0; x < 4; ++x) mma(s[x & 1], a[x & 1][x >> 1], qf[k2 + (x >> 1)]);
         }
         // element i of s[t2] is key 64kt + 32t2 + 16(i/8) + 8half + i%8
         float mx = -INFINITY;
@@ -139,14 +167,14 @@ __global__ __launch_bounds__(CB_NT) void coarse_fwd_kernel(const T* __restrict__
             float pv[8];
 #pragma unroll
             for (int i = 0; i < 8; ++i) pv[i] = s[kk >> 1][(kk & 1) * 8 + i];
+            F a[MT];
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) lds_frag_tr<RB, true>(a[mt], v_lds, mt * 32, kk * 16);
             pack_frag_hilo(pb, pl, pv);
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                F a;
-                lds_frag_tr<RB, true>(a, v_lds, mt * 32, kk * 16);
-                mma(oacc[mt], a, pb);
-                mma(oacc[mt], a, pl);
-            }
+            for (int mt = 0; mt < MT; ++mt) mma(oacc[mt], a[mt], pb);
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) mma(oacc[mt], a[mt], pl);
         }
     }
     const float lt = l + swap_half(l);
@@ -224,31 +252,47 @@ __global__ __launch_bounds__(CB_NT) void coarse_dkdv_kernel(const T* __restrict_
         for (int i = 0; i < 16; ++i) { acc_v[mt][i] = 0.f; acc_k[mt][i] = 0.f; }
 
     const int ntiles = (N + 63) / 64;
+    row_stage<RB, E == 2> qs_, os_;
+    auto head_of = [&](const T* base, int hl) {
+        return reinterpret_cast<const char*>(base + (b * Hq + hkv * grp + hl) * N * D);
+    };
+    qs_.fetch(head_of(qc, 0), 0, N, tid);
+    os_.fetch(head_of(doc, 0), 0, N, tid);
     for (int hl = 0; hl < grp; ++hl) {
         const int64_t bh = b * Hq + hkv * grp + hl;
         const char* qb = reinterpret_cast<const char*>(qc + bh * N * D);
         const char* ob = reinterpret_cast<const char*>(doc + bh * N * D);
         for (int qt = 0; qt < ntiles; ++qt) {
             __syncthreads();
-            load_rows_sync<RB, E == 2>(q_lds, qb, static_cast<int64_t>(qt) * 64, N, tid);
-            load_rows_sync<RB, E == 2>(o_lds, ob, static_cast<int64_t>(qt) * 64, N, tid);
+            qs_.store(q_lds, qb, static_cast<int64_t>(qt) * 64, N, tid);
+            os_.store(o_lds, ob, static_cast<int64_t>(qt) * 64, N, tid);
             if (tid < 64) {
                 const int64_t i = static_cast<int64_t>(qt) * 64 + tid;
                 st_lds[tid] = i < N ? stat[bh * N + i] : make_float2(INFINITY, 0.f);
             }
             __syncthreads();
+            if (qt + 1 < ntiles || hl + 1 < grp) {
+                const bool same = qt + 1 < ntiles;
+                const int64_t row0 = same ? static_cast<int64_t>(qt + 1) * 64 : 0;
+                qs_.fetch(head_of(qc, same ? hl : hl + 1), row0, N, tid);
+                os_.fetch(head_of(doc, same ? hl : hl + 1), row0, N, tid);
+            }
 #pragma unroll
             for (int qtile = 0; qtile < 2; ++qtile) {
                 f32x16_t s, dp;
 #pragma unroll
                 for (int i = 0; i < 16; ++i) { s[i] = 0.f; dp[i] = 0.f; }
 #pragma unroll
-                for (int ks = 0; ks < KS; ++ks) {
-                    F a;
-                    lds_frag_s<RB>(a, q_lds, qtile * 32 + (lane & 31), ks * 16 + half * 8);
-                    mma(s, a, kf[ks]);
-                    lds_frag_s<RB>(a, o_lds, qtile * 32 + (lane & 31), ks * 16 + half * 8);
-                    mma(dp, a, vf[ks]);
+                for (int k2 = 0; k2 < KS; k2 += 2) {
+                    F a[4];
+#pragma unroll
+                    for (int x = 0; x < 4; ++x)
+                        lds_frag_s<RB>(a[x], x & 1 ? o_lds : q_lds, qtile * 32 + (lane & 31),
+                                       (k2 + (x >> 1)) * 16 + half * 8);
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) {
+                        if (x & 1) mma(dp, a[x], vf[k2 + (x >> 1)]); else mma(s, a[x], kf[k2 + (x >> 1)]);
+                    }
                 }
                 // entry i is query 32qtile + 16(i/8) + 8half + i%8 of the tile
                 float pv[16], dsv[16];
@@ -269,13 +313,13 @@ __global__ __launch_bounds__(CB_NT) void coarse_dkdv_kernel(const T* __restrict_
                 for (int h2 = 0; h2 < 2; ++h2)
 #pragma unroll
                     for (int mt = 0; mt < MT; ++mt) {
-                        F a;
-                        lds_frag_tr<RB, true>(a, o_lds, mt * 32, (2 * qtile + h2) * 16);
-                        mma(acc_v[mt], a, pb[h2]);
-                        mma(acc_v[mt], a, pl[h2]);
-                        lds_frag_tr<RB, true>(a, q_lds, mt * 32, (2 * qtile + h2) * 16);
-                        mma(acc_k[mt], a, db[h2]);
-                        mma(acc_k[mt], a, dl[h2]);
+                        F av, ak;
+                        lds_frag_tr<RB, true>(av, o_lds, mt * 32, (2 * qtile + h2) * 16);
+                        lds_frag_tr<RB, true>(ak, q_lds, mt * 32, (2 * qtile + h2) * 16);
+                        mma(acc_v[mt], av, pb[h2]);
+                        mma(acc_k[mt], ak, db[h2]);
+                        mma(acc_v[mt], av, pl[h2]);
+                        mma(acc_k[mt], ak, dl[h2]);
                     }
             }
         }
@@ -340,11 +384,18 @@ __global__ __launch_bounds__(CB_NT) void coarse_dq_kernel(const T* __restrict__ 
     const char* kb = reinterpret_cast<const char*>(kc + kv * N * D);
     const char* vb = reinterpret_cast<const char*>(vc + kv * N * D);
     const int ntiles = (N + 63) / 64;
+    row_stage<RB, E == 2> ks_, vs_;
+    ks_.fetch(kb, 0, N, tid);
+    vs_.fetch(vb, 0, N, tid);
     for (int kt = 0; kt < ntiles; ++kt) {
         __syncthreads();
-        load_rows_sync<RB, E == 2>(k_lds, kb, static_cast<int64_t>(kt) * 64, N, tid);
-        load_rows_sync<RB, E == 2>(v_lds, vb, static_cast<int64_t>(kt) * 64, N, tid);
+        ks_.store(k_lds, kb, static_cast<int64_t>(kt) * 64, N, tid);
+        vs_.store(v_lds, vb, static_cast<int64_t>(kt) * 64, N, tid);
         __syncthreads();
+        if (kt + 1 < ntiles) {
+            ks_.fetch(kb, static_cast<int64_t>(kt + 1) * 64, N, tid);
+            vs_.fetch(vb, static_cast<int64_t>(kt + 1) * 64, N, tid);
+        }
 #pragma unroll
         for (int t2 = 0; t2 < 2; ++t2) {
             // S^T = K Q^T, dP^T = V dO^T: 32 keys x this lane's query
@@ -352,12 +403,16 @@ __global__ __launch_bounds__(CB_NT) void coarse_dq_kernel(const T* __restrict__ 
 #pragma unroll
             for (int i = 0; i < 16; ++i) { s[i] = 0.f; dp[i] = 0.f; }
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                F a;
-                lds_frag_s<RB>(a, k_lds, t2 * 32 + (lane & 31), ks * 16 + half * 8);
-                mma(s, a, qf[ks]);
-                lds_frag_s<RB>(a, v_lds, t2 * 32 + (lane & 31), ks * 16 + half * 8);
-                mma(dp, a, of[ks]);
+            for (int k2 = 0; k2 < KS; k2 += 2) {
+                F a[4];
+#pragma unroll
+                for (int x = 0; x < 4; ++x)
+                    lds_frag_s<RB>(a[x], x & 1 ? v_lds : k_lds, t2 * 32 + (lane & 31),
+                                   (k2 + (x >> 1)) * 16 + half * 8);
+#pragma unroll
+                for (int x = 0; x < 4; ++x) {
+                    if (x & 1) mma(dp, a[x], of[k2 + (x >> 1)]); else mma(s, a[x], qf[k2 + (x >> 1)]);
+                }
             }
             float ds[16];
 #pragma unroll
@@ -372,11 +427,15 @@ __global__ __launch_bounds__(CB_NT) void coarse_dq_kernel(const T* __restrict__ 
 #pragma unroll
             for (int h2 = 0; h2 < 2; ++h2)
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt) {
-                    F a;
-                    lds_frag_tr<RB, true>(a, k_lds, mt * 32, (2 * t2 + h2) * 16);
-                    mma(dqa[mt], a, sb[h2]);
-                    mma(dqa[mt], a, sl[h2]);
+                for (int m2 = 0; m2 < MT; m2 += 2) {
+                    F a[2];
+#pragma unroll
+                    for (int x = 0; x < 2; ++x)
+                        lds_frag_tr<RB, true>(a[x], k_lds, (m2 + x) * 32, (2 * t2 + h2) * 16);
+#pragma unroll
+                    for (int x = 0; x < 2; ++x) mma(dqa[m2 + x], a[x], sb[h2]);
+#pragma unroll
+                    for (int x = 0; x < 2; ++x) mma(dqa[m2 + x], a[x], sl[h2]);
                 }
         }
     }
