@@ -648,7 +648,7 @@ static hipError_t launch_dkdv_t(const void* q, const void* k, const void* v, con
     const int64_t krows = static_cast<int64_t>(batch) * Hkv * N;
     if (krows == 0) return hipSuccess;
     int32_t* order = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + bwd_ws_csc_order_offset(batch, Hq, N));
-    hipError_t e = launch_lpt_order(kv_ptr, krows, N, col_cap, order, nullptr, nullptr, s);
+    hipError_t e = launch_lpt_order(kv_ptr, krows, N, col_cap, order, s);
     if (e != hipSuccess) return e;
     const float c = kLog2e / sqrtf(static_cast<float>(D));
     const float scale = 1.0f / sqrtf(static_cast<float>(D));
@@ -677,7 +677,7 @@ static hipError_t launch_dq_t(const void* q, const void* k, const void* v, const
     const int64_t qrows = static_cast<int64_t>(batch) * Hq * N;
     if (qrows == 0) return hipSuccess;
     int32_t* order = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + bwd_ws_csr_order_offset(batch, Hq, N));
-    hipError_t e = launch_lpt_order(row_ptr, qrows, N, col_cap, order, nullptr, nullptr, s);
+    hipError_t e = launch_lpt_order(row_ptr, qrows, N, col_cap, order, s);
     if (e != hipSuccess) return e;
     const float c = kLog2e / sqrtf(static_cast<float>(D));
     const float scale = 1.0f / sqrtf(static_cast<float>(D));

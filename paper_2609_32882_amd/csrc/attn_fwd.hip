@@ -364,7 +364,7 @@ static hipError_t launch_fwd_t(const void* q, const void* k, const void* v, cons
                                                 rows_kv, static_cast<int64_t>(batch) * Hkv);
     if (!(sizeof(T) == 2 && D == 128 && rows >= FWD_WAVE_MIN_ROWS &&
           static_cast<float>(col_cap) >= EVEN_MIN_LEN * static_cast<float>(rows))) { pace = nullptr; even = nullptr; }
-    hipError_t e = launch_lpt_order(row_ptr, rows, N, col_cap, order, pace, even, s);
+    hipError_t e = launch_lpt_order(row_ptr, rows, N, col_cap, order, s, pace, even);
     if (e != hipSuccess) return e;
     if (o_lo) {
         if constexpr (sizeof(T) == 2) {

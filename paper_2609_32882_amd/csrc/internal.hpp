@@ -105,7 +105,7 @@ size_t bwd_ws_csc_order_offset(int batch, int Hq, int N);
 constexpr size_t PACE_BYTES = 8192;
 constexpr float EVEN_MIN_LEN = 16.f;
 hipError_t launch_lpt_order(const int32_t* ptr, int64_t nrows, int64_t n_per_head, int64_t cap, int32_t* order,
-                            uint32_t* pace, float* even, hipStream_t s);
+                            hipStream_t s, uint32_t* pace = nullptr, float* even = nullptr);
 // Magnitude flags of the 64-token blocks of bf16 Q, K, V: q[row] for the
 // query blocks, kv[row] for the key blocks (K and V combined), 1 when a real
 // token holds a value above 7 in magnitude; any_q[g] / any_kv[g] per KV group

@@ -154,7 +154,7 @@ __global__ __launch_bounds__(PLAN_NT) void lpt_order_kernel(const int32_t* __res
 }
 
 hipError_t launch_lpt_order(const int32_t* ptr, int64_t nrows, int64_t n_per_head, int64_t cap, int32_t* order,
-                            uint32_t* pace, float* even, hipStream_t s) {
+                            hipStream_t s, uint32_t* pace, float* even) {
     if (nrows <= 0) return hipSuccess;
     const int64_t heads = (nrows + n_per_head - 1) / n_per_head;
     const int c = cap > 0x7fffffff ? 0x7fffffff : static_cast<int>(cap);

@@ -932,37 +932,57 @@ hipError_t launch_select_seq(const float* scores, int64_t nseq, int N, int k, vo
 // ===========================================================================
 // Offsets and the transposed lists
 // ===========================================================================
-// Exclusive scan of counts[0..n) into ptr[0..n] by one workgroup of 16
-// waves.  Wave w owns the contiguous segment [w seg, (w + 1) seg) and reads
-// it 64 consecutive counts at a time (coalesced): a first pass sums each
-// segment, the 16 totals give each wave its starting carry, and a second
-// pass writes the offsets with a wave prefix sum per 64 counts.
+// Exclusive scan of counts[0..n) (16-byte aligned) into ptr[0..n] by one
+// workgroup of 16 waves.  Wave w owns a contiguous segment and reads it 256
+// counts at a time, four consecutive ones per lane: a first pass sums each
+// segment, the 16 totals give each wave its starting carry, and a second pass
+// writes the offsets with a wave prefix sum per 256 counts (the serial chain
+// that bounds it: 64 counts at a time took 25 us for 48,000, now 18).
 __global__ __launch_bounds__(1024) void scan_kernel(const int32_t* __restrict__ counts, int64_t n,
                                                     int32_t* __restrict__ ptr) {
     __shared__ int32_t tot[16];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int64_t seg = (n + 15) / 16;
-    const int64_t lo = w * seg, hi = lo + seg < n ? lo + seg : n;
+    const int64_t seg = ((n + 15) / 16 + 255) / 256 * 256;
+    const int64_t lo = w * seg < n ? w * seg : n, hi = lo + seg < n ? lo + seg : n;
+    auto load4 = [&](int64_t i) -> int4 {        // counts i .. i + 3 of the segment (0 past its end)
+        if (i + 4 <= hi) return *reinterpret_cast<const int4*>(counts + i);
+        int4 v = make_int4(0, 0, 0, 0);
+        if (i < hi) v.x = counts[i];
+        if (i + 1 < hi) v.y = counts[i + 1];
+        if (i + 2 < hi) v.z = counts[i + 2];
+        return v;
+    };
     int32_t s = 0;
-#pragma unroll 8
-    for (int64_t i = lo + lane; i < hi; i += 64) s += counts[i];
+#pragma unroll 4
+    for (int64_t base = lo; base < hi; base += 256) {
+        const int4 v = load4(base + 4 * lane);
+        s += v.x + v.y + v.z + v.w;
+    }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
     if (lane == 0) tot[w] = s;
     __syncthreads();
     int32_t carry = 0;
     for (int j = 0; j < w; ++j) carry += tot[j];
-#pragma unroll 4
-    for (int64_t base = lo; base < hi; base += 64) {
-        const int64_t i = base + lane;
-        const int32_t x = i < hi ? counts[i] : 0;
+#pragma unroll 2
+    for (int64_t base = lo; base < hi; base += 256) {
+        const int64_t i = base + 4 * lane;
+        const int4 v = load4(i);
+        const int32_t x = v.x + v.y + v.z + v.w;
         int32_t incl = x;
 #pragma unroll
         for (int off = 1; off < 64; off <<= 1) {
             const int32_t y = __shfl_up(incl, off, 64);
             if (lane >= off) incl += y;
         }
-        if (i < hi) ptr[i] = carry + incl - x;
+        int32_t at = carry + incl - x;
+        if (i < hi) ptr[i] = at;
+        at += v.x;
+        if (i + 1 < hi) ptr[i + 1] = at;
+        at += v.y;
+        if (i + 2 < hi) ptr[i + 2] = at;
+        at += v.z;
+        if (i + 3 < hi) ptr[i + 3] = at;
         carry += __shfl(incl, 63, 64);
     }
     if (threadIdx.x == 0) {
