@@ -205,8 +205,8 @@ vsa2_status vsa2_route(const vsa2_problem* p, const vsa2_select* s,
                        float* block_scores, void* ws, size_t ws_bytes, hipStream_t stream);
 
 /* Bytes of workspace vsa2_attn_fwd (pass 0: the work order, one int32 per
- * CSR row, 8 KB of pacing words, one float per query head, and one byte per
- * query and key block for the large-magnitude flags), vsa2_attn_bwd (pass 1: two fp32 values per query token, its LSE
+ * CSR row, for 2,048 rows and up 8 KB of pacing words and one float per query
+ * head, and one byte per query and key block for the large-magnitude flags), vsa2_attn_bwd (pass 1: two fp32 values per query token, its LSE
  * and its Delta, the work orders of the CSR and CSC rows, the flags and one
  * more byte per query block for the row flags, see vsa2_attn_bwd) or
  * vsa2_coarse_bwd (pass 2: one fp32 pair per coarse query) needs.  The
@@ -268,11 +268,11 @@ vsa2_status vsa2_attn_fwd(const vsa2_problem* p, const void* q, const void* k, c
  * of the library instead of a caller buffer.  The call allocates nothing.
  *   Arguments as for vsa2_attn_fwd, without ws / ws_bytes; the stream's
  *   device must be the current device.
- *   Limit: the array holds VSA2_NOALLOC_SCRATCH_BYTES (2 MiB) per GPU, for
+ *   Limit: the array holds VSA2_NOALLOC_SCRATCH_BYTES per GPU, for
  *   as long as the process runs; a problem whose forward workspace
  *   (vsa2_attn_workspace(p, 0)) is larger returns VSA2_ERR_WORKSPACE before
  *   any device work (about 6 bytes per query-block row: up to about
- *   347,000 rows batch * heads_q * blocks with heads_kv = heads_q).
+ *   349,000 rows batch * heads_q * blocks with heads_kv = heads_q).
  *   Every call on one GPU uses that GPU's one array: calls that overlap on
  *   one GPU (concurrent streams, or two graphs replayed at once) race and
  *   must be ordered by the caller.  Each call rewrites all of the array it
@@ -280,7 +280,7 @@ vsa2_status vsa2_attn_fwd(const vsa2_problem* p, const void* q, const void* k, c
  * Errors: as for vsa2_attn_fwd; VSA2_ERR_WORKSPACE for a problem beyond the
  *   limit; VSA2_ERR_HIP if the array's device address cannot be obtained.
  */
-#define VSA2_NOALLOC_SCRATCH_BYTES ((size_t)2 << 20)
+#define VSA2_NOALLOC_SCRATCH_BYTES (((size_t)2 << 20) + ((size_t)128 << 10))
 vsa2_status vsa2_attn_fwd_noalloc(const vsa2_problem* p, const void* q, const void* k, const void* v,
                                   const int32_t* row_ptr, const int32_t* col_idx, int64_t col_cap,
                                   void* o, float* lse, void* o_lo, hipStream_t stream);

@@ -324,17 +324,6 @@ static void launch_fwd_k(const void* q, const void* k, const void* v, const int3
                        resident_per_xcd<attn_fwd_kernel<T, D, COMP, PAD>>(AF_NT), order, even, cg, fl);
 }
 
-// Forward workspace: the work order of the CSR rows (one int32 per row), the
-// one-wave kernel's pacing words and the heads it takes (one float per query
-// head), then the block magnitude flags (used when the call keeps O's remainder).
-static size_t align256f(size_t x) { return (x + 255) / 256 * 256; }
-
-size_t fwd_workspace_bytes(int batch, int Hq, int Hkv, int N) {
-    const int64_t rq = static_cast<int64_t>(batch) * Hq * N, rkv = static_cast<int64_t>(batch) * Hkv * N;
-    return align256f(4 * static_cast<size_t>(rq)) + PACE_BYTES + align256f(4 * static_cast<size_t>(batch) * Hq) +
-           block_flags_bytes(rq, rkv, static_cast<int64_t>(batch) * Hkv);
-}
-
 // Rows from which bf16 problems with D = 128 also launch the one-wave kernel,
 // which takes the heads with even lists (about one length, 16 entries and up):
 // it keeps a SIMD per row, so it needs the chip's 1,024 SIMDs twice over, and
@@ -348,6 +337,23 @@ size_t fwd_workspace_bytes(int batch, int Hq, int Hkv, int N) {
 // per row), so both stay here.
 constexpr int64_t FWD_WAVE_MIN_ROWS = 2048;
 
+// Forward workspace: the work order of the CSR rows (one int32 per row); for
+// problems that may take the one-wave kernel its pacing words and the heads it
+// takes (one float per query head); then the block magnitude flags (used when
+// the call keeps O's remainder).
+static size_t align256f(size_t x) { return (x + 255) / 256 * 256; }
+
+static size_t fwd_wave_bytes(int batch, int Hq, int N) {
+    if (static_cast<int64_t>(batch) * Hq * N < FWD_WAVE_MIN_ROWS || N < EVEN_MIN_LEN) return 0;
+    return PACE_BYTES + align256f(4 * static_cast<size_t>(batch) * Hq);
+}
+
+size_t fwd_workspace_bytes(int batch, int Hq, int Hkv, int N) {
+    const int64_t rq = static_cast<int64_t>(batch) * Hq * N, rkv = static_cast<int64_t>(batch) * Hkv * N;
+    return align256f(4 * static_cast<size_t>(rq)) + fwd_wave_bytes(batch, Hq, N) +
+           block_flags_bytes(rq, rkv, static_cast<int64_t>(batch) * Hkv);
+}
+
 template <typename T, int D>
 static hipError_t launch_fwd_t(const void* q, const void* k, const void* v, const int32_t* row_ptr,
                                const int32_t* col_idx, int64_t col_cap, void* o, float* lse, void* o_lo,
@@ -360,9 +366,9 @@ static hipError_t launch_fwd_t(const void* q, const void* k, const void* v, cons
     char* at = static_cast<char*>(ws) + align256f(4 * static_cast<size_t>(rows));
     uint32_t* pace = reinterpret_cast<uint32_t*>(at);
     float* even = reinterpret_cast<float*>(at + PACE_BYTES);
-    const block_flag_layout fl = block_flags_at(at + PACE_BYTES + align256f(4 * static_cast<size_t>(batch) * Hq), rows,
-                                                rows_kv, static_cast<int64_t>(batch) * Hkv);
-    if (!(sizeof(T) == 2 && D == 128 && rows >= FWD_WAVE_MIN_ROWS &&
+    const size_t wave_bytes = fwd_wave_bytes(batch, Hq, N);
+    const block_flag_layout fl = block_flags_at(at + wave_bytes, rows, rows_kv, static_cast<int64_t>(batch) * Hkv);
+    if (!(sizeof(T) == 2 && D == 128 && wave_bytes &&
           static_cast<float>(col_cap) >= EVEN_MIN_LEN * static_cast<float>(rows))) { pace = nullptr; even = nullptr; }
     hipError_t e = launch_lpt_order(row_ptr, rows, N, col_cap, order, s, pace, even);
     if (e != hipSuccess) return e;
