@@ -318,6 +318,11 @@ __device__ __forceinline__ int byte_val(int32_t w, int64_t i) { return (w >> (8 
 // compiler's own wait-count bookkeeping, which cannot tell the LDS buffers
 // apart, does not put a full vmcnt(0) wait in front of every LDS read; the
 // kernels order these copies themselves with vm_wait and wg_barrier.
+// Nor does it see what the two instructions need around them: the load takes
+// its LDS base from M0 one instruction after M0 is written at the earliest, and
+// its address from SGPRs that no vector instruction (a readfirstlane) wrote
+// within five.  The s_mov_b64 between them is both: the wait state, and a
+// scalar copy of the address, which the hardware orders by itself.
 __device__ __forceinline__ void dma16(uint32_t lds, const void* base, int voff) {
     // readfirstlane works on (signed) 32-bit ints: both halves go back through
     // uint32_t so the low word is zero-extended, never sign-extended.
@@ -326,8 +331,9 @@ __device__ __forceinline__ void dma16(uint32_t lds, const void* base, int voff) 
     const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(b >> 32)));
     const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(b & 0xffffffffu)));
     const uint64_t bs = (static_cast<uint64_t>(hi) << 32) | static_cast<uint64_t>(lo);
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :
+    uint64_t at;
+    asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dwordx4 %2, %0"
+                 : "=&s"(at)
                  : "s"(l), "v"(voff), "s"(bs)
                  : "memory", "m0");
 }
@@ -348,24 +354,25 @@ __device__ __forceinline__ void dma16_run(uint32_t lds, uint64_t base, const int
     const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(base >> 32)));
     const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(base & 0xffffffffu)));
     const uint64_t bs = (static_cast<uint64_t>(hi) << 32) | static_cast<uint64_t>(lo);
+    uint64_t at;
     if constexpr (NR == 1)
-        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
-                     : : "s"(l), "v"(voff[0]), "s"(bs) : "memory", "m0");
+        asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %2\n\tglobal_load_lds_dwordx4 %3, %0"
+                     : "=&s"(at) : "s"(l), "s"(bs), "v"(voff[0]) : "memory", "m0");
     else if constexpr (NR == 2)
-        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %3\n\t"
-                     "global_load_lds_dwordx4 %2, %3 offset:1024"
-                     : : "s"(l), "v"(voff[0]), "v"(voff[1]), "s"(bs) : "memory", "m0");
+        asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %2\n\tglobal_load_lds_dwordx4 %3, %0\n\t"
+                     "global_load_lds_dwordx4 %4, %0 offset:1024"
+                     : "=&s"(at) : "s"(l), "s"(bs), "v"(voff[0]), "v"(voff[1]) : "memory", "m0");
     else if constexpr (NR == 3)
-        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %4\n\t"
-                     "global_load_lds_dwordx4 %2, %4 offset:1024\n\t"
-                     "global_load_lds_dwordx4 %3, %4 offset:2048"
-                     : : "s"(l), "v"(voff[0]), "v"(voff[1]), "v"(voff[2]), "s"(bs) : "memory", "m0");
+        asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %2\n\tglobal_load_lds_dwordx4 %3, %0\n\t"
+                     "global_load_lds_dwordx4 %4, %0 offset:1024\n\t"
+                     "global_load_lds_dwordx4 %5, %0 offset:2048"
+                     : "=&s"(at) : "s"(l), "s"(bs), "v"(voff[0]), "v"(voff[1]), "v"(voff[2]) : "memory", "m0");
     else
-        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %5\n\t"
-                     "global_load_lds_dwordx4 %2, %5 offset:1024\n\t"
-                     "global_load_lds_dwordx4 %3, %5 offset:2048\n\t"
-                     "global_load_lds_dwordx4 %4, %5 offset:3072"
-                     : : "s"(l), "v"(voff[0]), "v"(voff[1]), "v"(voff[2]), "v"(voff[3]), "s"(bs)
+        asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %2\n\tglobal_load_lds_dwordx4 %3, %0\n\t"
+                     "global_load_lds_dwordx4 %4, %0 offset:1024\n\t"
+                     "global_load_lds_dwordx4 %5, %0 offset:2048\n\t"
+                     "global_load_lds_dwordx4 %6, %0 offset:3072"
+                     : "=&s"(at) : "s"(l), "s"(bs), "v"(voff[0]), "v"(voff[1]), "v"(voff[2]), "v"(voff[3])
                      : "memory", "m0");
 }
 

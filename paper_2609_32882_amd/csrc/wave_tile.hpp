@@ -51,10 +51,11 @@ struct wave_copy {
         const uint64_t b = g + (J / 4) * 4096;
         const uint32_t l = lds + (J / 4) * 4096;
         const int o = live ? off[J % 4] : 0;
-        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3"
-                     :
+        uint64_t at;                              // the waits of dma16
+        asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dwordx4 %2, %0 offset:%4"
+                     : "=&s"(at)
                      : "s"(l), "v"(o), "s"(b), "n"((J % 4) * 1024)
-                     : "memory");
+                     : "memory", "m0");
     }
 };
 
@@ -173,10 +174,11 @@ struct pace_clock {
     // The words, on their way to LDS (one vector-memory operation).
     __device__ __forceinline__ void request() const {
         const uint32_t l = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_void_t*)copy));
-        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2 sc1"
-                     :
+        uint64_t from;
+        asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dwordx4 %2, %0 sc1"
+                     : "=&s"(from)
                      : "s"(l), "v"(static_cast<int>(threadIdx.x * 16)), "s"(words)
-                     : "memory");
+                     : "memory", "m0");
     }
     __device__ __forceinline__ void store(uint32_t x) const {
         asm volatile("s_mov_b64 exec, 1\n\tglobal_store_dword %0, %1, %2\n\ts_mov_b64 exec, -1"
