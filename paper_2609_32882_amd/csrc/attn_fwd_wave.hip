@@ -141,6 +141,7 @@ __global__ __launch_bounds__(64, 1) void attn_fwd_wave_kernel(
     // the list, 64 entries at a time in a register (lane i: entry 64 w + i of
     // the walk); entries outside [0, N) read as -1
     int ents = -1;
+    bool any = false;                 // an entry inside [0, N) was met
     auto load_ents = [&](int w) {
         const int j = 64 * w + lane;
         int c = -1;
@@ -149,6 +150,7 @@ __global__ __launch_bounds__(64, 1) void attn_fwd_wave_kernel(
             c = col_idx[e0 + (t >= cnt ? t - cnt : t)];
         }
         ents = (c >= 0 && c < N) ? c : -1;
+        any = any || __ballot(ents >= 0) != 0;
     };
     auto walk = [&](auto two_term) {
         constexpr bool TWO = decltype(two_term)::value;
@@ -314,7 +316,7 @@ __global__ __launch_bounds__(64, 1) void attn_fwd_wave_kernel(
                 for (int e = 0; e < 32; ++e) {
                     const int qt = (e >> 3) & 1;
                     const float sv = s[T][qt][8 * (e >> 4) + (e & 7)];
-                    x[e] = m[qt] == -INFINITY ? 0.f : fast_exp2(fmaf(sv, c_log2, -m[qt]));
+                    x[e] = sv == -INFINITY ? 0.f : fast_exp2(fmaf(sv, c_log2, -m[qt]));   // NaN stays
                     el_sum(e);
                 }
             }
@@ -418,7 +420,9 @@ __global__ __launch_bounds__(64, 1) void attn_fwd_wave_kernel(
         const bool q_real = !PAD || ((qmask >> (32 * qt + (lane & 31))) & 1);
         const float lt = q_real ? l[qt] + swap_half(l[qt]) : 0.f;     // a padding query has no output
         const float lrt = q_real ? lr[qt] + swap_half(lr[qt]) : 0.f;
-        const float inv = lrt > 0.f ? 1.0f / lrt : 0.f;
+        // keys but no score above -inf: no weights to divide by
+        const float none = any && m[qt] == -INFINITY ? __builtin_nanf("") : 0.f;
+        const float inv = lrt > 0.f ? 1.0f / lrt : none;
         const int64_t tok = qtok + 32 * qt;
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)

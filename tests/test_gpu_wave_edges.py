@@ -1,0 +1,140 @@
+"""The one-wave forward where its shortcuts could show: values that are not
+finite, entries outside [0, N), heads that fall to either kernel in one call,
+and rows of a few entries among paced ones.
+
+The same heads computed in one call (one-wave: 2,048 rows and up) and in two
+halves (two-wave); test_gpu_wave.py derives the tolerance."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2609_32882_amd as vsa2
+from parity import MAX_ABS, REL_L2, ULP_REL, value_errors
+from test_gpu_wave import slice_lists
+from workload import Problem
+
+pytestmark = pytest.mark.gpu
+
+PACE_BYTES = 8192
+INF, NAN = float("inf"), float("nan")
+
+
+def align256(n):
+    return (n + 255) // 256 * 256
+
+
+def forward(p, q, k, v, rp, ci, training):
+    """O (with its remainder when training), LSE as numpy, and the per-head
+    average list lengths that the library's rule stored (0: two-wave), or None
+    below 2,048 rows.  Outputs are prefilled, so a row that no kernel writes shows."""
+    P = vsa2.problem_from(p)
+    st, wsb = vsa2.vsa2_attn_workspace(P, 0)
+    assert st == 0
+    ws = torch.zeros(wsb, dtype=torch.uint8, device="cuda")
+    fill = 1.25e30
+    o, o_lo = torch.full_like(q, fill), torch.full_like(q, fill)
+    lse = torch.full((p.batch, p.heads_q, p.L_joint), fill, device="cuda")
+    st = vsa2.vsa2_attn_fwd(P, q.data_ptr(), k.data_ptr(), v.data_ptr(), rp.data_ptr(), ci.data_ptr(), ci.numel(),
+                            o.data_ptr(), lse.data_ptr(), o_lo.data_ptr() if training else None, ws.data_ptr(), wsb,
+                            torch.cuda.current_stream().cuda_stream)
+    assert st == 0, vsa2.STATUS_NAMES[st]
+    rows, even = p.batch * p.heads_q * p.N_joint, None
+    if rows >= 2048:
+        at = align256(4 * rows) + PACE_BYTES
+        even = ws[at:at + 4 * p.batch * p.heads_q].view(torch.float32).cpu().numpy()
+    out = o.float() + o_lo.float() if training else o.float()
+    assert not (o.float() == torch.tensor(fill).bfloat16().float().item()).any() and not (lse == fill).any()
+    return out.cpu().numpy(), lse.cpu().numpy(), even
+
+
+def halves(p, q, k, v, rp, ci, training):
+    h, hkv, out = p.heads_q // 2, p.heads_kv // 2, []
+    ph = p.replace(heads_q=h, heads_kv=hkv)
+    for i in range(2):
+        r, c = slice_lists(dict(row_ptr=rp, col_idx=ci), p.N_joint, i * h, (i + 1) * h)
+        cut = [t[:, i * s:(i + 1) * s].contiguous() for t, s in ((q, h), (k, hkv), (v, hkv))]
+        o, lse, even = forward(ph, *cut, r, c, training)
+        assert even is None
+        out.append((o, lse))
+    return [np.concatenate([a[j] for a in out], 1) for j in range(2)]
+
+
+def assert_same(got, want):
+    """Equal where not finite (any NaN for NaN), within the bar elsewhere."""
+    (o, lse), (o2, lse2) = got, want
+    assert np.array_equal(np.isnan(o), np.isnan(o2)), "NaN at %d and %d values" % (np.isnan(o).sum(), np.isnan(o2).sum())
+    inf = np.isinf(o2)
+    assert np.array_equal(np.isinf(o), inf) and np.array_equal(o[inf], o2[inf])
+    fin = np.isfinite(o2)
+    _, beyond, rel = value_errors(o[fin], o2[fin], 2 * ULP_REL["bf16"])
+    assert beyond <= 2 * MAX_ABS and rel <= REL_L2, (beyond, rel)
+    assert np.array_equal(np.isnan(lse), np.isnan(lse2)) and np.array_equal(np.isinf(lse), np.isinf(lse2))
+    fin = np.isfinite(lse2)
+    assert np.array_equal(np.sign(lse[np.isinf(lse)]), np.sign(lse2[np.isinf(lse)]))
+    assert np.abs(lse[fin] - lse2[fin]).max() <= 2e-5 * max(1.0, np.abs(lse2[fin]).max())
+
+
+def lists_of(rows, device="cuda"):
+    """CSR of a list of int arrays."""
+    rp = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int32)
+    return torch.from_numpy(rp).to(device), torch.from_numpy(np.concatenate(rows).astype(np.int32)).to(device)
+
+
+def inputs(p, seed):
+    """Q, K, V in bf16, N(0, 1) (padding tokens too: they may hold anything finite)."""
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    return [torch.randn((p.batch, h, p.L_joint, p.head_dim), generator=g, device="cuda").bfloat16()
+            for h in (p.heads_q, p.heads_kv, p.heads_kv)]
+
+
+def random_rows(p, k, seed):
+    g = np.random.default_rng(seed)
+    return [np.sort(g.choice(p.N, k, replace=False)) for _ in range(p.heads_q * p.N)]
+
+
+# problems that the one-wave kernel takes: 352 blocks unpadded, 352 and (for training) 900 with cut cubes
+FLAT = Problem(1, 6, 6, 128, 16, 44, 32, dtype=1)
+CUT = {False: Problem(1, 6, 6, 128, 15, 42, 30, dtype=1), True: Problem(1, 4, 4, 128, 18, 58, 46, dtype=1)}
+LEN = 50                       # entries a row, long enough for either
+
+
+def poison(what, q, k, v):
+    """Puts values that are not finite into the second head of each half."""
+    blk = lambda n: slice(64 * n, 64 * n + 64)
+    for h in (1, q.shape[1] // 2 + 1):
+        if what == "nan-query":
+            q[0, h, 69, 17] = NAN                      # one query of block 1
+        elif what == "inf-query":
+            q[0, h, 69, 17] = INF
+        elif what == "nan-key-block":
+            k[0, h, blk(0)] = NAN                      # first in every list that holds it
+        elif what == "nan-key":
+            k[0, h, 64 * 5 + 40, 3] = NAN
+        elif what == "inf-keys":
+            k[0, h, 0:32, 3] = INF                     # half a block: scores of +inf and -inf
+        elif what == "inf-keys-late":
+            k[0, h, 64 * 20:64 * 20 + 32, 3] = -INF
+        elif what == "all-scores-infinite":
+            k[0, h, :, 3] = INF
+        elif what == "nan-value":
+            v[0, h, 64 * 6 + 1, 9] = NAN
+        elif what == "inf-value":
+            v[0, h, 64 * 6 + 1, 9] = -INF
+
+
+@pytest.mark.parametrize("training", [False, True])
+@pytest.mark.parametrize("what", ["nan-query", "inf-query", "nan-key-block", "nan-key", "inf-keys", "inf-keys-late",
+                                  "all-scores-infinite", "nan-value", "inf-value"])
+def test_values_that_are_not_finite_pass_as_in_the_two_wave_kernel(what, training):
+    """A NaN is never turned into a number, an infinite score has weight 0 or
+    makes its row NaN, and other rows are untouched."""
+    for p in (FLAT, CUT[training]):
+        q, k, v = inputs(p, 91)
+        rp, ci = lists_of(random_rows(p, LEN, 92))
+        poison(what, q, k, v)
+        print("\n[%s] %s" % (what, p), flush=True)
+        o, lse, even = forward(p, q, k, v, rp, ci, training)
+        assert (even == LEN).all()
+        want = halves(p, q, k, v, rp, ci, training)
+        assert (~np.isfinite(want[0])).any()
+        assert_same((o, lse), want)
