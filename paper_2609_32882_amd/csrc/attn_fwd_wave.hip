@@ -40,6 +40,11 @@ __device__ __forceinline__ void for_each_ic(Fn&& fn) {
     }
 }
 
+// The V tile of an entry outside [0, N): its scores are masked, and its
+// probabilities, all 0, need a V whose products are 0 (a real tile may hold
+// infinities), so that the entry can go through the pipeline like any other.
+__device__ const uint4 zero_tile[2 * wave_copy<256>::HALF / 16] = {};
+
 template <bool COMP, bool PAD>
 __global__ __launch_bounds__(64, 1) void attn_fwd_wave_kernel(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
@@ -159,14 +164,16 @@ __global__ __launch_bounds__(64, 1) void attn_fwd_wave_kernel(
         u32x4_t pw[2][2][2][PT];      // P fragments: [t][kk][qt][hi, lo], 4 words each
         F ring[4];
 
-        // block of walk position j (wave-uniform); positions past the list
-        // and malformed entries use block 0 and are not live / masked
+        // block of walk position j (wave-uniform); -1 for positions past the
+        // list (not live) and entries outside [0, N), which copy block 0's K
+        // (masked) and a V of zeros
         auto ent_at = [&](int j) -> int { return __builtin_amdgcn_readlane(ents, j & 63); };
 
         struct src { uint64_t k, v; bool live; };
+        const uint64_t zb = reinterpret_cast<uint64_t>(zero_tile);
         auto src_of = [&](int c, bool live) {
             const int64_t at = static_cast<int64_t>(c < 0 ? 0 : c) * TILE;
-            return src{kb + at, vb + at, live};
+            return src{kb + at, c < 0 ? zb : vb + at, live};
         };
         auto fetch_row = [&](auto f, int t, int ks) { fr.row(ring[decltype(f)::value & 3], k_lds, t, ks); };
         auto fetch_col = [&](auto f, int t, int u) { fr.col(ring[decltype(f)::value & 3], v_lds, t, u / MT, u % MT); };

@@ -138,3 +138,34 @@ def test_values_that_are_not_finite_pass_as_in_the_two_wave_kernel(what, trainin
         want = halves(p, q, k, v, rp, ci, training)
         assert (~np.isfinite(want[0])).any()
         assert_same((o, lse), want)
+
+
+@pytest.mark.parametrize("training", [False, True])
+def test_entries_outside_the_range_read_nothing(training):
+    """Entries outside [0, N) at the first, middle and last places, in a head
+    whose block 0 (in no list) holds infinities and NaN: finite, and as the
+    lists without those entries give."""
+    for p in (FLAT, CUT[training]):
+        q, k, v = inputs(p, 93)
+        blk0 = slice(0, 64)
+        k[:, :, blk0] = NAN
+        v[:, ::2, blk0] = INF
+        v[:, 1::2, blk0] = NAN
+        g = np.random.default_rng(94)
+        rows, holes = [], []
+        for i in range(p.heads_q * p.N):
+            r = np.sort(1 + g.choice(p.N - 1, LEN, replace=False))
+            rows.append(r)
+            bad = [-1, p.N, 2 ** 30, -2 ** 31]
+            h = np.insert(r, [0, 8], [bad[i % 4], bad[(i + 1) % 4]])
+            holes.append(np.append(h, bad[(i + 2) % 4]) if i % 2 else h)
+        rows[5], holes[5] = rows[5][:0], np.full(LEN + 2, -1)          # a row of nothing else
+        rp, ci = lists_of(holes)
+        o, lse, even = forward(p, q, k, v, rp, ci, training)
+        assert (even > 0).all()
+        assert np.isfinite(o).all() and not np.isnan(lse).any()
+        # the same lists without the entries, on a head count below the rule: two-wave
+        want = halves(p, q, k, v, *lists_of(rows), training)
+        assert_same((o, lse), want)
+        row5 = slice(5 * 64, 6 * 64)
+        assert (o[0, 0, row5] == 0).all() and np.isneginf(lse[0, 0, row5]).all()
