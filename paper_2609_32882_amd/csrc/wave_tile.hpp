@@ -181,8 +181,9 @@ struct pace_clock {
                      : "memory", "m0");
     }
     __device__ __forceinline__ void store(uint32_t x) const {
-        asm volatile("s_mov_b64 exec, 1\n\tglobal_store_dword %0, %1, %2\n\ts_mov_b64 exec, -1"
-                     :
+        uint64_t active;                          // put back as it was
+        asm volatile("s_mov_b64 %0, exec\n\ts_mov_b64 exec, 1\n\tglobal_store_dword %1, %2, %3\n\ts_mov_b64 exec, %0"
+                     : "=&s"(active)
                      : "v"(at), "v"(x), "s"(words)
                      : "memory");
     }

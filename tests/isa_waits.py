@@ -96,6 +96,23 @@ def parse(listing: str) -> dict[str, list[Instr]]:
     return kernels
 
 
+def exec_constants(code) -> list[str]:
+    """Hand-written writes of EXEC that put a constant there and do not put back
+    what they found: the compiler does not see them, so the lanes that it had
+    switched off would run on.  Allowed is a copy of EXEC, the constant, and
+    the copy back before any branch."""
+    out = []
+    for n, i in enumerate(code):
+        if i.op != "s_mov_b64" or not re.fullmatch(r"exec, 1", i.args):
+            continue
+        kept = re.fullmatch(r"(s\[\d+:\d+\]), exec", code[n - 1].args) if n else None
+        back = next((j for j in code[n + 1:] if j.args.startswith("exec") or j.op.startswith(("s_cbranch", "s_branch"))),
+                    None)
+        if not (kept and code[n - 1].op == "s_mov_b64" and back and back.args == "exec, " + kept[1]):
+            out.append("%s %s" % (i.op, i.args))
+    return out
+
+
 def _before(code, n, states):
     """Instructions that can run fewer than `states` wait states before n."""
     best, todo = {}, [(p, 0) for p in code[n].preds]

@@ -49,3 +49,29 @@ def test_the_built_kernels_keep_their_waits(tmp_path):
     assert sum(bool(i.acc) for k in kernels for c in k.values() for i in c) > 100
     found = [v for x in listings for v in isa_waits.violations(x)]
     assert not found, "%d missing waits, first: %s" % (len(found), found[:3])
+
+
+EXEC = """
+0000000000001000 <k>:
+%s
+\ts_mov_b64 exec, 1                                          // 000000001004: BEFE0181
+\tglobal_store_dword v1, v2, s[4:5]                          // 000000001008: DC708000 00040201
+\ts_mov_b64 exec, %s                                         // 000000001010: BEFE0106
+\ts_endpgm                                                   // 000000001014: BF810000
+"""
+KEPT = "\ts_mov_b64 s[6:7], exec                                     // 000000001000: BE86017E"
+
+
+@pytest.mark.parametrize("first,back,found", [(KEPT, "s[6:7]", 0), (KEPT, "-1", 1), (KEPT, "s[8:9]", 1), (NOP0, "s[6:7]", 1)])
+def test_the_check_finds_lanes_left_switched(first, back, found):
+    assert len(isa_waits.exec_constants(isa_waits.parse(EXEC % (first, back))["k"])) == found
+
+
+def test_the_built_kernels_put_their_lanes_back(tmp_path):
+    if not os.path.exists(build.LIB):
+        build.build()
+    codes = [c for x in isa_waits.disassemble(build.LIB, str(tmp_path)) for c in isa_waits.parse(x).values()]
+    # the pacing words' stores: there are some
+    assert sum(i.op == "s_mov_b64" and i.args == "exec, 1" for c in codes for i in c) > 0
+    found = [v for c in codes for v in isa_waits.exec_constants(c)]
+    assert not found, found[:3]
