@@ -22,9 +22,12 @@ namespace vsa2 {
 // sequence of Lj tokens: the N*B video tokens, then any text tokens): all
 // Pt*Ph*Pw of them unless the grid is padded, where the real tokens of a
 // sub-cube form a box and an all-padding sub-cube pools to 0.
-// FP = 2, 4: sub-cubes of 2 x 2 x 2 (the router's pool) or 4 x 4 x 4 tokens
-// (the whole cube: the coarse branch, VSA's router), their 8 (16 a layer) loads
-// unrolled and issued together; FP = 0: any sub-cube (runtime loops).
+// FP = 2, 4: sub-cubes of 2 x 2 x 2 (the router's pool) or, in bf16, 4 x 4 x 4
+// tokens (the whole cube: the coarse branch, VSA's router), their 8 (16 a layer)
+// loads unrolled and issued together; FP = 0: any sub-cube (runtime loops).  An
+// fp32 token is two loads, and a layer of 32 in flight is no faster than the
+// loops: 64 whole cubes 16.1 us against 12.9, 9,600 of D = 128 65.0 against 63.9
+// (in bf16 9.1 against 14.6, 35.8 against 38.5).
 // HBM-bound; I is the index type (64-bit divisions by N and G cost as much as
 // the sums, so launches below 2^31 threads take 32-bit ones).  786 MB pooled:
 // as whole cubes 167 -> 151 us, as 2 x 2 x 2 sub-cubes 180 -> 172 us.
@@ -132,7 +135,7 @@ hipError_t launch_pool(int dtype, const void* x, void* out, int64_t nbh, int N, 
     };
     auto with = [&](auto elem, auto index) {
         if (Pt == 2 && Ph == 2 && Pw == 2) go(elem, std::integral_constant<int, 2>{}, index);
-        else if (Pt == 4 && Ph == 4 && Pw == 4) go(elem, std::integral_constant<int, 4>{}, index);
+        else if (Pt == 4 && Ph == 4 && Pw == 4) go(elem, std::integral_constant<int, sizeof(elem) == 2 ? 4 : 0>{}, index);
         else go(elem, std::integral_constant<int, 0>{}, index);
     };
     // the last block's threads past nthreads must not wrap either
