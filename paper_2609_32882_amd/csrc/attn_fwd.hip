@@ -56,11 +56,13 @@ __global__ __launch_bounds__(AF_NT, 2) void attn_fwd_kernel(
 
     const int tid = threadIdx.x, lane = tid & 63, wave = wave_id(), half = lane >> 5;
     const int64_t item = xcd_item(blockIdx.x, gridDim.x);
-    const int64_t bh = item / N;             // the order permutes rows within a head
+    // the order permutes rows within a head; a grid's size fits in 32 bits
+    const int64_t bh = static_cast<uint32_t>(item) / static_cast<uint32_t>(N);
     if (even && even[bh] > 0.f) return;      // a head of the one-wave kernel
     const int64_t row = work_row(order, item, gridDim.x);
-    const int n = static_cast<int>(row % N);
-    const int b = static_cast<int>(bh / Hq), h = static_cast<int>(bh % Hq);
+    const int n = static_cast<int>(row - bh * N);
+    const int b = static_cast<int>(static_cast<uint32_t>(bh) / static_cast<uint32_t>(Hq));
+    const int h = static_cast<int>(bh) - b * Hq;
     const int hkv = h / (Hq / Hkv);
     const int64_t L = static_cast<int64_t>(N) * 64;
     const char* kb = reinterpret_cast<const char*>(k + static_cast<int64_t>(b * Hkv + hkv) * L * D);

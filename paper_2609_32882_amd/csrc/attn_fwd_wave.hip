@@ -66,12 +66,14 @@ __global__ __launch_bounds__(64, 1) void attn_fwd_wave_kernel(
 
     const int lane = threadIdx.x, half = lane >> 5;
     const int64_t item = xcd_item(blockIdx.x, gridDim.x);
-    const int64_t bh = item / N;             // the order permutes rows within a head
+    // the order permutes rows within a head; a grid's size fits in 32 bits
+    const int64_t bh = static_cast<uint32_t>(item) / static_cast<uint32_t>(N);
     const float avg = even[bh];              // this head's average list length
     if (!(avg > 0.f)) return;                // uneven lists: a head of the two-wave kernel
     const int64_t row = work_row(order, item, gridDim.x);
-    const int n = static_cast<int>(row % N);
-    const int b = static_cast<int>(bh / Hq), h = static_cast<int>(bh % Hq);
+    const int n = static_cast<int>(row - bh * N);
+    const int b = static_cast<int>(static_cast<uint32_t>(bh) / static_cast<uint32_t>(Hq));
+    const int h = static_cast<int>(bh) - b * Hq;
     const int64_t kvh = static_cast<int64_t>(b) * Hkv + h / (Hq / Hkv);
     const int64_t L = static_cast<int64_t>(N) * 64;
     const uint64_t kb = reinterpret_cast<uint64_t>(k + kvh * L * D), vb = reinterpret_cast<uint64_t>(v + kvh * L * D);
