@@ -205,12 +205,13 @@ vsa2_status vsa2_route(const vsa2_problem* p, const vsa2_select* s,
                        float* block_scores, void* ws, size_t ws_bytes, hipStream_t stream);
 
 /* Bytes of workspace vsa2_attn_fwd (pass 0: the work order, one int32 per
- * CSR row, for 2,048 rows and up 8 KB of pacing words and one float per query
- * head, and one byte per query and key block for the large-magnitude flags), vsa2_attn_bwd (pass 1: two fp32 values per query token, its LSE
- * and its Delta, the work orders of the CSR and CSC rows, the flags and one
- * more byte per query block for the row flags, see vsa2_attn_bwd) or
- * vsa2_coarse_bwd (pass 2: one fp32 pair per coarse query) needs.  The
- * work order lists the rows of each XCD's range longest first (a stable
+ * CSR row; for 2,048 rows and up of at least 320 blocks a head, or 6,144 rows
+ * of at least 216, 8 KB of pacing words and one float per query head; and one
+ * byte per query and key block for the large-magnitude flags), vsa2_attn_bwd
+ * (pass 1: two fp32 values per query token, its LSE and its Delta, the work
+ * orders of the CSR and CSC rows, the flags and one more byte per query block
+ * for the row flags, see vsa2_attn_bwd) or vsa2_coarse_bwd (pass 2: one fp32
+ * pair per coarse query) needs.  The work order lists the rows of each XCD's range longest first (a stable
  * counting sort by length class), so the launch's last workgroups are
  * short ones; rows of equal length keep their order. */
 vsa2_status vsa2_attn_workspace(const vsa2_problem* p, int32_t pass, size_t* bytes);
@@ -264,8 +265,9 @@ vsa2_status vsa2_attn_fwd(const vsa2_problem* p, const void* q, const void* k, c
  * vsa2_attn_fwd_noalloc - vsa2_attn_fwd for callers that cannot allocate
  * device memory (code under HIP graph capture, serving loops or harnesses
  * that forbid hipMalloc): the same computation and results, bit for bit,
- * with the call's workspace (work order and block flags) in a fixed array
- * of the library instead of a caller buffer.  The call allocates nothing.
+ * with the call's workspace (work order, pacing words and heads' averages,
+ * block flags) in a fixed array of the library instead of a caller buffer.
+ * The call allocates nothing.
  *   Arguments as for vsa2_attn_fwd, without ws / ws_bytes; the stream's
  *   device must be the current device.
  *   Limit: the array holds VSA2_NOALLOC_SCRATCH_BYTES per GPU, for

@@ -326,18 +326,37 @@ static void launch_fwd_k(const void* q, const void* k, const void* v, const int3
                        resident_per_xcd<attn_fwd_kernel<T, D, COMP, PAD>>(AF_NT), order, even, cg, fl);
 }
 
-// Rows from which bf16 problems with D = 128 also launch the one-wave kernel,
-// which takes the heads with even lists (about one length, 16 entries and up):
-// it keeps a SIMD per row, so it needs the chip's 1,024 SIMDs twice over, and
-// its fixed cost per row is not hidden by another wave.  Measured, us, this
-// kernel -> that one, top-k lists of k entries:
-//   rows      1,024 k 24   2,048 k 24   2,240 k 70   8,960 k 70   48,000 k 120
-//             78 -> 77     157 -> 147   504 -> 457   1627 -> 1434  15300 -> 13460
-//   below:    512 k 24 66 -> 69, 1,024 k 8 39 -> 43
-// Uneven lists (mass selection) ran 2-25% slower there, since nothing keeps
-// their walks together, and D = 64 5-25% (half the work per gathered byte and
-// per row), so both stay here.
+// Which bf16 problems with D = 128 also launch the one-wave kernel, which takes
+// the heads with even lists (about one length).  It keeps a SIMD per row, so it
+// needs the chip's 1,024 SIMDs twice over; its fixed cost per row is not hidden
+// by another wave, so the lists must not be short, the less the more rows there
+// are (the two-wave kernel's rounds overlap); and it gains by keeping the walks
+// together, so a head's K and V must be well beyond an XCD's L2 (4 MB, 128
+// blocks).  Measured, us, two-wave -> one-wave kernel, N blocks a head, top-k
+// lists of k entries (inference; training the same within 3%):
+//   taken    N   320  rows  2,240  k 32   223 ->  219, k 80   490 ->  487
+//            N   240  rows  6,720  k 24   441 ->  423, k 80  1281 -> 1192
+//            N   560  rows  8,960  k 32   793 ->  735, k 80  1828 -> 1631
+//            N 1,200  rows  4,800  k 24   431 ->  366, k 80  1278 ->  915
+//            N 1,200  rows 48,000  k 48  6532 -> 6238, k 120  14500 -> 13200
+//   left     N    33  rows  2,112  k 24   159 ->  178
+//            N   180  rows  2,160  k 24   167 ->  175, k 80   463 ->  489
+//            N   180  rows  7,200  k 60  1110 -> 1131
+//            N   240  rows  2,160  k 32   211 ->  217, k 80   464 ->  485
+//            N 1,200  rows 28,800  k 16  1598 -> 1695, k 24  2215 -> 2264
+//            N 1,200  rows 38,400 (grouped heads)  k 32  3575 -> 3633
+// Of 336 problems measured that the rule takes, none lost more than 1%.
+// Left to the two-wave kernel as well: uneven lists (mass selection, 2-25%
+// slower there, since nothing keeps their walks together), D = 64 (5-25%, half
+// the work per gathered byte and per row), and in training the heads most of
+// whose rows take two-term P (N 180, rows 2,160, k 45: 399 -> 447; N 560, rows
+// 6,720, k 18: 510 -> 553; N 1,200, rows 28,800, k 120: 11785 -> 11849).
 constexpr int64_t FWD_WAVE_MIN_ROWS = 2048;
+constexpr int FWD_WAVE_MIN_BLOCKS = 320;              // below FWD_WAVE_FEW_ROWS rows
+constexpr int64_t FWD_WAVE_FEW_ROWS = 6144;
+constexpr int FWD_WAVE_MIN_BLOCKS_ROWS = 216;         // from there on
+
+static float fwd_wave_min_len(int64_t rows) { return rows < 8192 ? 24.f : rows < 24576 ? 32.f : 48.f; }
 
 // Forward workspace: the work order of the CSR rows (one int32 per row); for
 // problems that may take the one-wave kernel its pacing words and the heads it
@@ -346,7 +365,9 @@ constexpr int64_t FWD_WAVE_MIN_ROWS = 2048;
 static size_t align256f(size_t x) { return (x + 255) / 256 * 256; }
 
 static size_t fwd_wave_bytes(int batch, int Hq, int N) {
-    if (static_cast<int64_t>(batch) * Hq * N < FWD_WAVE_MIN_ROWS || N < EVEN_MIN_LEN) return 0;
+    const int64_t rows = static_cast<int64_t>(batch) * Hq * N;
+    if (rows < FWD_WAVE_MIN_ROWS || N < (rows < FWD_WAVE_FEW_ROWS ? FWD_WAVE_MIN_BLOCKS : FWD_WAVE_MIN_BLOCKS_ROWS))
+        return 0;
     return PACE_BYTES + align256f(4 * static_cast<size_t>(batch) * Hq);
 }
 
@@ -366,23 +387,31 @@ static hipError_t launch_fwd_t(const void* q, const void* k, const void* v, cons
     const int64_t rows_kv = static_cast<int64_t>(batch) * Hkv * N;
     int32_t* order = static_cast<int32_t*>(ws);
     char* at = static_cast<char*>(ws) + align256f(4 * static_cast<size_t>(rows));
-    uint32_t* pace = reinterpret_cast<uint32_t*>(at);
-    float* even = reinterpret_cast<float*>(at + PACE_BYTES);
     const size_t wave_bytes = fwd_wave_bytes(batch, Hq, N);
     const block_flag_layout fl = block_flags_at(at + wave_bytes, rows, rows_kv, static_cast<int64_t>(batch) * Hkv);
-    if (!(sizeof(T) == 2 && D == 128 && wave_bytes &&
-          static_cast<float>(col_cap) >= EVEN_MIN_LEN * static_cast<float>(rows))) { pace = nullptr; even = nullptr; }
-    hipError_t e = launch_lpt_order(row_ptr, rows, N, col_cap, order, s, pace, even);
-    if (e != hipSuccess) return e;
+    wave_heads wave;
+    wave.min_len = fwd_wave_min_len(rows);
+    if (sizeof(T) == 2 && D == 128 && wave_bytes &&
+        static_cast<float>(col_cap) >= wave.min_len * static_cast<float>(rows)) {
+        wave.pace = reinterpret_cast<uint32_t*>(at);
+        wave.even = reinterpret_cast<float*>(at + PACE_BYTES);
+        wave.flag_q = o_lo ? fl.q : nullptr;
+        wave.flag_kv = o_lo ? fl.kv : nullptr;
+        wave.group = Hq / Hkv;
+    }
+    const float* even = wave.even;
+    hipError_t e = hipSuccess;
     if (o_lo) {
         if constexpr (sizeof(T) == 2) {
             e = launch_block_flags(q, k, v, fl, rows, rows_kv, N, D, Hq, Hkv, cg, s);
             if (e != hipSuccess) return e;
         }
     }
+    e = launch_lpt_order(row_ptr, rows, N, col_cap, order, s, wave);
+    if (e != hipSuccess) return e;
     if (even) {
-        e = launch_attn_fwd_wave(q, k, v, row_ptr, col_idx, col_cap, o, lse, o_lo, order, pace, even, rows, Hq, Hkv, N,
-                                 cg, fl, s);
+        e = launch_attn_fwd_wave(q, k, v, row_ptr, col_idx, col_cap, o, lse, o_lo, order, wave.pace, even, rows, Hq,
+                                 Hkv, N, cg, fl, s);
         if (e != hipSuccess) return e;
     }
     if (o_lo) {

@@ -90,8 +90,9 @@ hipError_t launch_attn_fwd(int dtype, int D, const void* q, const void* k, const
                            const int32_t* row_ptr, const int32_t* col_idx, int64_t col_cap, void* o,
                            float* lse, void* o_lo, void* ws, int batch, int Hq, int Hkv, int N,
                            const cube_grid& cg, hipStream_t s);
-// Forward workspace: the work order of the CSR rows (int32 per row), then the
-// block magnitude flags.
+// Forward workspace: the work order of the CSR rows (int32 per row); for sizes
+// that may take the one-wave kernel, its pacing words and one float per query
+// head (whether that kernel takes it); then the block magnitude flags.
 size_t fwd_workspace_bytes(int batch, int Hq, int Hkv, int N);
 // Backward workspace: (LSE*log2 e, Delta) per query token, then the work
 // orders of the CSR rows (dQ) and of the CSC rows (dK/dV).
@@ -100,12 +101,18 @@ size_t bwd_ws_csr_order_offset(int batch, int Hq, int N);
 size_t bwd_ws_csc_order_offset(int batch, int Hq, int N);
 // Longest-first work order of the rows of ptr within each piece of a head
 // (n_per_head rows) that falls into one XCD range.
-// pace (may be null): the pacing words of the launch that follows, cleared; even:
-// per head, the average list length when its lists are even, else 0.
 constexpr size_t PACE_BYTES = 8192;
-constexpr float EVEN_MIN_LEN = 16.f;
+// What the call needs to know before the one-wave forward (even null: nothing).
+struct wave_heads {
+    uint32_t* pace = nullptr;            // its pacing words, cleared
+    float* even = nullptr;               // per query head that it takes, the average list length, else 0
+    float min_len = 0.f;                 // shortest average taken
+    const uint8_t* flag_q = nullptr;     // training: the block magnitude flags (block_flag_layout)
+    const uint8_t* flag_kv = nullptr;
+    int group = 1;                       // query heads per KV head
+};
 hipError_t launch_lpt_order(const int32_t* ptr, int64_t nrows, int64_t n_per_head, int64_t cap, int32_t* order,
-                            hipStream_t s, uint32_t* pace = nullptr, float* even = nullptr);
+                            hipStream_t s, const wave_heads& wave = wave_heads{});
 // Magnitude flags of the 64-token blocks of bf16 Q, K, V: q[row] for the
 // query blocks, kv[row] for the key blocks (K and V combined), 1 when a real
 // token holds a value above 7 in magnitude; any_q[g] / any_kv[g] per KV group

@@ -123,29 +123,43 @@ __device__ void lpt_segment(const int32_t* __restrict__ ptr, int cap, int32_t* _
 // of 32 rows, 11 us for 40 heads of 1,200.)
 __global__ __launch_bounds__(PLAN_NT) void lpt_order_kernel(const int32_t* __restrict__ ptr, int64_t nrows,
                                                             int64_t n_per_head, int cap,
-                                                            int32_t* __restrict__ order,
-                                                            uint32_t* __restrict__ pace,
-                                                            float* __restrict__ even) {
+                                                            int32_t* __restrict__ order, wave_heads wave) {
     __shared__ uint32_t hist[PLAN_CLASSES][PLAN_NT];
     __shared__ int lens[PLAN_KEPT];
     __shared__ int red[PLAN_NT / 64];
     const int64_t h0 = static_cast<int64_t>(blockIdx.x) * n_per_head;
     const int64_t h1 = h0 + n_per_head < nrows ? h0 + n_per_head : nrows;
     const int x = blockIdx.y;
-    if (pace && x == 7) {
-        // clears the pacing words of the launch that follows, and says whether
-        // this head's lists are even: at least EVEN_MIN_LEN entries on average,
-        // 7 of 8 rows within 1/16 of the average (then the average, else 0)
+    if (wave.even && x == 7) {
+        // clears the pacing words of the launch that follows, and decides whether
+        // the one-wave forward takes this head (then its average list length is
+        // stored, else 0): lists of at least min_len entries on average, 7 of 8
+        // rows within 1/16 of the average, and, in the training forward, not most
+        // of its rows with two-term products (a flagged query block, or among
+        // avg key blocks, f of all N flagged, one that is: 1 - (1 - f)^avg
+        // passes 1/2 at f avg of about 0.7)
         if (blockIdx.x == 0)
-            for (int i = threadIdx.x; i < static_cast<int>(PACE_BYTES / 4); i += PLAN_NT) pace[i] = 0u;
+            for (int i = threadIdx.x; i < static_cast<int>(PACE_BYTES / 4); i += PLAN_NT) wave.pace[i] = 0u;
         const int n = static_cast<int>(h1 - h0);
         const int total = min(max(ptr[h1], 0), cap) - min(max(ptr[h0], 0), cap);
         const float avg = static_cast<float>(total) / static_cast<float>(n);
-        int near = 0;
-        for (int i = threadIdx.x; i < n; i += PLAN_NT)
+        const int64_t kv0 = blockIdx.x / wave.group * n_per_head;
+        int near = 0, q = 0, kv = 0;
+        for (int i = threadIdx.x; i < n; i += PLAN_NT) {
+            if (wave.flag_q) {
+                q += wave.flag_q[h0 + i];
+                kv += wave.flag_kv[kv0 + i];
+            }
             near += fabsf(static_cast<float>(row_len(ptr, h0 + i, cap)) - avg) <= avg * (1.f / 16) ? 1 : 0;
+        }
         near = wg_reduce(near, red, [](int a, int b) { return a + b; });
-        if (threadIdx.x == 0) even[blockIdx.x] = avg >= EVEN_MIN_LEN && near >= n - n / 8 ? avg : 0.f;
+        bool take = avg >= wave.min_len && near >= n - n / 8;
+        if (wave.flag_q && take) {
+            q = wg_reduce(q, red, [](int a, int b) { return a + b; });
+            kv = wg_reduce(kv, red, [](int a, int b) { return a + b; });
+            take = 2 * q <= n && static_cast<float>(kv) * avg <= 0.7f * static_cast<float>(n);
+        }
+        if (threadIdx.x == 0) wave.even[blockIdx.x] = take ? avg : 0.f;
     }
     const int64_t q = nrows >> 3, r = nrows & 7;
     const int64_t xs = x * q + (x < r ? x : r), xe = xs + q + (x < r ? 1 : 0);
@@ -154,12 +168,12 @@ __global__ __launch_bounds__(PLAN_NT) void lpt_order_kernel(const int32_t* __res
 }
 
 hipError_t launch_lpt_order(const int32_t* ptr, int64_t nrows, int64_t n_per_head, int64_t cap, int32_t* order,
-                            hipStream_t s, uint32_t* pace, float* even) {
+                            hipStream_t s, const wave_heads& wave) {
     if (nrows <= 0) return hipSuccess;
     const int64_t heads = (nrows + n_per_head - 1) / n_per_head;
     const int c = cap > 0x7fffffff ? 0x7fffffff : static_cast<int>(cap);
     hipLaunchKernelGGL(lpt_order_kernel, dim3(static_cast<unsigned>(heads), 8), dim3(PLAN_NT), 0, s, ptr, nrows,
-                       n_per_head, c, order, pace, even);
+                       n_per_head, c, order, wave);
     return hipGetLastError();
 }
 

@@ -4,7 +4,8 @@ the guards must hold the pattern unchanged (no write before the start or past
 the end of any buffer), and the outputs must match the same calls made on
 plain tensors bit for bit.  Cases: a padded grid (the masked kernel
 variants), GQA with mass selection on skewed inputs (large-magnitude blocks),
-fp32, and joint video + text sequences."""
+fp32, joint video + text sequences, and calls large enough for the one-wave
+forward, unpadded and padded."""
 import numpy as np
 import pytest
 import torch
@@ -25,6 +26,9 @@ CASES = {
                                          skewed=True),
     "f32-d128": Workload("g3", Problem(1, 2, 1, 128, 4, 16, 16, dtype=F32), Selection(0, 5), 7003),
     "bf16-text100": Workload("g4", Problem(1, 2, 2, 128, 8, 16, 24, text_len=100), Selection(0, 12), 7004),
+    # even lists, 2,048 rows and up of 320 blocks and up: the one-wave forward, its pacing words and heads' averages
+    "bf16-wave": Workload("g5", Problem(1, 8, 8, 128, 12, 44, 40), Selection(0, 24), 7005),
+    "bf16-wave-padded": Workload("g6", Problem(1, 8, 2, 128, 15, 42, 30), Selection(0, 25), 7006),
 }
 
 

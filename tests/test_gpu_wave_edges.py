@@ -1,6 +1,7 @@
 """The one-wave forward where its shortcuts could show: values that are not
-finite, entries outside [0, N), heads that fall to either kernel in one call,
-and rows of a few entries among paced ones.
+finite, entries outside [0, N), heads that fall to either kernel in one call
+(uneven lists, large-magnitude blocks), and rows of a few entries among paced
+ones.
 
 The same heads computed in one call (one-wave: 2,048 rows and up) and in two
 halves (two-wave); test_gpu_wave.py derives the tolerance."""
@@ -8,43 +9,13 @@ import numpy as np
 import pytest
 import torch
 
-import paper_2609_32882_amd as vsa2
 from parity import MAX_ABS, REL_L2, ULP_REL, value_errors
-from test_gpu_wave import slice_lists
+from test_gpu_wave import forward, one_wave_heads, slice_lists
 from workload import Problem
 
 pytestmark = pytest.mark.gpu
 
-PACE_BYTES = 8192
 INF, NAN = float("inf"), float("nan")
-
-
-def align256(n):
-    return (n + 255) // 256 * 256
-
-
-def forward(p, q, k, v, rp, ci, training):
-    """O (with its remainder when training), LSE as numpy, and the per-head
-    average list lengths that the library's rule stored (0: two-wave), or None
-    below 2,048 rows.  Outputs are prefilled, so a row that no kernel writes shows."""
-    P = vsa2.problem_from(p)
-    st, wsb = vsa2.vsa2_attn_workspace(P, 0)
-    assert st == 0
-    ws = torch.zeros(wsb, dtype=torch.uint8, device="cuda")
-    fill = 1.25e30
-    o, o_lo = torch.full_like(q, fill), torch.full_like(q, fill)
-    lse = torch.full((p.batch, p.heads_q, p.L_joint), fill, device="cuda")
-    st = vsa2.vsa2_attn_fwd(P, q.data_ptr(), k.data_ptr(), v.data_ptr(), rp.data_ptr(), ci.data_ptr(), ci.numel(),
-                            o.data_ptr(), lse.data_ptr(), o_lo.data_ptr() if training else None, ws.data_ptr(), wsb,
-                            torch.cuda.current_stream().cuda_stream)
-    assert st == 0, vsa2.STATUS_NAMES[st]
-    rows, even = p.batch * p.heads_q * p.N_joint, None
-    if rows >= 2048:
-        at = align256(4 * rows) + PACE_BYTES
-        even = ws[at:at + 4 * p.batch * p.heads_q].view(torch.float32).cpu().numpy()
-    out = o.float() + o_lo.float() if training else o.float()
-    assert not (o.float() == torch.tensor(fill).bfloat16().float().item()).any() and not (lse == fill).any()
-    return out.cpu().numpy(), lse.cpu().numpy(), even
 
 
 def halves(p, q, k, v, rp, ci, training):
@@ -134,7 +105,9 @@ def test_values_that_are_not_finite_pass_as_in_the_two_wave_kernel(what, trainin
         poison(what, q, k, v)
         print("\n[%s] %s" % (what, p), flush=True)
         o, lse, even = forward(p, q, k, v, rp, ci, training)
-        assert (even == LEN).all()
+        assert np.array_equal(even, one_wave_heads(p, rp, (q, k, v) if training else None))
+        # in training, a head whose key blocks are all flagged is the two-wave kernel's
+        assert (even == LEN).sum() == p.heads_q - (2 if training and what == "all-scores-infinite" else 0)
         want = halves(p, q, k, v, rp, ci, training)
         assert (~np.isfinite(want[0])).any()
         assert_same((o, lse), want)
@@ -169,3 +142,69 @@ def test_entries_outside_the_range_read_nothing(training):
         assert_same((o, lse), want)
         row5 = slice(5 * 64, 6 * 64)
         assert (o[0, 0, row5] == 0).all() and np.isneginf(lse[0, 0, row5]).all()
+
+
+@pytest.mark.parametrize("training", [False, True])
+def test_heads_of_both_kernels_in_one_call(training):
+    """Every other head has uneven lists (12 to 88 entries) and stays with the
+    two-wave kernel; one head is even but for an eighth of its rows, one has one
+    more such row."""
+    for p in (FLAT, CUT[training]):
+        q, k, v = inputs(p, 95)
+        g = np.random.default_rng(96)
+        rows = random_rows(p, LEN, 97)
+        for h in range(1, p.heads_q, 2):
+            for i in range(h * p.N, (h + 1) * p.N):
+                rows[i] = np.sort(g.choice(p.N, int(g.integers(12, 89)), replace=False))
+        # heads at the edge of the rule: long rows (the average, LEN + 1/2, is what
+        # counts; LEN + 4 is more than 1/16 off it)
+        for h, n in ((0, p.N // 8), (2, p.N // 8 + 1)):
+            for i in range(h * p.N, h * p.N + n):
+                rows[i] = np.sort(g.choice(p.N, LEN + 4, replace=False))
+        rp, ci = lists_of(rows)
+        o, lse, even = forward(p, q, k, v, rp, ci, training)
+        want_even = one_wave_heads(p, rp)
+        assert np.array_equal(even > 0, want_even > 0) and np.allclose(even, want_even, rtol=1e-6)
+        assert even[0] > 0 and even[2] == 0 and not (even[1::2] > 0).any() and (even[4::2] > 0).all()
+        assert_same((o, lse), halves(p, q, k, v, rp, ci, training))
+
+
+def test_heads_with_large_magnitude_blocks():
+    """Training: two-term P in the one-wave kernel where few blocks are flagged;
+    from 0.7 flagged key blocks an average list, or from half of the query
+    blocks, the head is the two-wave kernel's."""
+    for p in (FLAT, CUT[True]):
+        q, k, v = inputs(p, 101)
+        rp, ci = lists_of(random_rows(p, LEN, 102))
+        g = np.random.default_rng(103)
+        most = int(0.7 * p.N / LEN)
+        flag = lambda x, h, n: [x[0, h, 64 * i + 21].mul_(12) for i in g.choice(p.N, n, replace=False)]
+        flag(k, 0, most)
+        flag(v, 1, most + 1)
+        flag(q, 2, p.N // 2)
+        flag(q, 3, p.N // 2 + 1)
+        o, lse, even = forward(p, q, k, v, rp, ci, True)
+        want = one_wave_heads(p, rp, (q, k, v))
+        assert np.array_equal(even, want) and [x > 0 for x in even[:4]] == [True, False, True, False]
+        assert_same((o, lse), halves(p, q, k, v, rp, ci, True))
+        _, _, plain = forward(p, q, k, v, rp, ci, False)               # inference: one-term P everywhere
+        assert (plain == LEN).all()
+
+
+@pytest.mark.parametrize("training", [False, True])
+def test_rows_of_few_entries_among_paced_ones(training):
+    """Rows of 0, 1, 2, 3, 63, 64 and 65 entries and of every block, spread over
+    even heads: the pipeline without its loop, a list window's edges, and walks
+    that are not paced."""
+    for p in (FLAT, CUT[training]):
+        q, k, v = inputs(p, 98)
+        g = np.random.default_rng(99)
+        rows = random_rows(p, LEN, 100)
+        odd = [0, 1, 2, 3, 63, 64, 65, p.N]
+        for h in range(p.heads_q):
+            for j, n in enumerate(g.choice(p.N, 24, replace=False)):
+                rows[h * p.N + n] = np.sort(g.choice(p.N, odd[(h + j) % len(odd)], replace=False))
+        rp, ci = lists_of(rows)
+        o, lse, even = forward(p, q, k, v, rp, ci, training)
+        assert (even > 0).all() and np.allclose(even, one_wave_heads(p, rp), rtol=1e-6)
+        assert_same((o, lse), halves(p, q, k, v, rp, ci, training))

@@ -16,6 +16,12 @@ from workload import Problem, Selection, Workload, make_inputs
 # then a smaller one with GQA and a padded grid
 CASES = [Workload("na1", Problem(1, 4, 2, 128, 8, 16, 24), Selection(1, 0, 0.9, 20), 5001, skewed=True),
          Workload("na2", Problem(1, 2, 1, 64, 5, 10, 15), Selection(0, 4), 5002)]
+# 2,048 rows and up of 320 blocks and up: the array also holds the pacing words and the heads' average
+# list lengths.  Even lists (one-wave forward), then uneven ones of the same rows
+# (two-wave), then even ones on a padded grid
+WAVE = [Workload("na3", Problem(1, 8, 8, 128, 12, 44, 40), Selection(0, 24), 5003),
+        Workload("na4", Problem(1, 8, 8, 128, 12, 44, 40), Selection(1, 0, 0.9, 60), 5004, skewed=True),
+        Workload("na5", Problem(1, 8, 2, 128, 15, 42, 30), Selection(0, 25), 5005)]
 
 
 def _bits(t):
@@ -60,12 +66,21 @@ def test_noalloc_forward_matches_workspace_forward_twice():
 
 
 @pytest.mark.gpu
-def test_noalloc_forward_in_a_hip_graph():
+def test_noalloc_forward_matches_workspace_forward_for_one_wave_rows():
+    for w in (*WAVE, WAVE[0]):
+        print("\n[no-alloc forward] %s" % w.problem, flush=True)
+        _run(w)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("w,w2", [CASES, WAVE[:2], WAVE[1::-1], WAVE[1:]],
+                         ids=["small", "even-then-uneven", "uneven-then-even", "uneven-then-padded"])
+def test_noalloc_forward_in_a_hip_graph(w, w2):
     """The call captured in a HIP graph (it allocates nothing, so it can be):
     three replays, each after eager work that refills the outputs with NaN
     and runs the allocation-free forward of another problem (which rewrites
-    the library's array), give the eager call's bits every time."""
-    w, w2 = CASES
+    the library's array: other flags, and at the larger sizes other pacing words and
+    heads of the other kernel), give the eager call's bits every time."""
     p, p2 = w.problem, w2.problem
     print("\n[no-alloc forward in a graph] %s" % p, flush=True)
 
