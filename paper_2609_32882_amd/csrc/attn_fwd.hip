@@ -338,7 +338,7 @@ static void launch_fwd_k(const void* q, const void* k, const void* v, const int3
 //            N   240  rows  6,720  k 24   441 ->  423, k 80  1281 -> 1192
 //            N   560  rows  8,960  k 32   793 ->  735, k 80  1828 -> 1631
 //            N 1,200  rows  4,800  k 24   431 ->  366, k 80  1278 ->  915
-//            N 1,200  rows 48,000  k 48  6532 -> 6238, k 120  14500 -> 13200
+//            N 1,200  rows 48,000  k 48  6532 -> 6238, k 120  15105 -> 13736
 //   left     N    33  rows  2,112  k 24   159 ->  178
 //            N   180  rows  2,160  k 24   167 ->  175, k 80   463 ->  489
 //            N   180  rows  7,200  k 60  1110 -> 1131

@@ -20,8 +20,8 @@
 //    three of the four are in flight.
 //  - Paced walks (wave_tile.hpp): the waves of an XCD stay within a few list
 //    entries of each other.  Unpaced, this kernel outruns the L2s: 139 GB of
-//    misses, 19.9 ms; paced 54 GB, 13.4 ms (14.9 ms for the two-wave kernel);
-//    with every gather an L2 hit 11.5 ms.
+//    misses, 19.9 ms; paced 54 GB, 13.2 to 13.8 ms a call by the box (14.5 to
+//    15.1 ms for the two-wave kernel); with every gather an L2 hit 11.5 ms.
 #include <type_traits>
 
 #include "wave_tile.hpp"

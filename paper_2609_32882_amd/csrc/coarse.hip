@@ -8,9 +8,9 @@
 //
 // The coarse attention is small (N x N per head, N = number of cubes, not a
 // multiple of 64 in general), so its kernels favour simplicity: tiles of 64
-// cube rows are loaded synchronously into padded, slot-permuted LDS rows
-// (the layout the fragment readers of the fine kernels expect), rows past N
-// read as zero and are masked out of every softmax.
+// cube rows go through registers into padded, slot-permuted LDS rows (the
+// layout the fragment readers of the two-wave kernels expect), bf16 ones read
+// one tile ahead; rows past N read as zero and are masked out of every softmax.
 #include "common.hpp"
 #include "internal.hpp"
 
@@ -23,9 +23,14 @@ constexpr float kLog2eC = 1.4426950408889634f;
 // tile, LDS row r holding global row row0 + tile_row_at(r) (bf16: column groups
 // in the cgroup_pos order the fragment readers expect); rows >= nrows are zero.
 // bf16 tiles are read one tile ahead into registers (fetch), so the reads are in
-// flight during the products of the tile before; fp32 ones, twice the size, are
-// read where they are stored.  The grid is at most one round of workgroups
-// (760 at 720p), so nothing else hides them.
+// flight during the products of the tile before.  That takes registers (D = 128:
+// the forward 190 -> 298, the query side 234 -> 323, so one wave per SIMD
+// instead of two, and the 760 workgroups of a 720p layer run in two rounds of
+// 512) and is the faster all the same: coarse branch and merge of 12 heads of
+// 560 cubes 460 -> 264 us.  fp32 tiles, twice the size, are read where they are
+// stored, all of a tile's reads in flight at once: the key side takes 512
+// registers and spills 12 bytes, and 8 heads of 1,200 cubes take 2,306 us
+// against 2,369 with those reads in a loop of 231 to 368 registers.
 template <int RB, bool CPERM>
 struct row_stage {
     static constexpr int CH = RB / 16, PER = 64 * CH / CB_NT;
@@ -117,8 +122,8 @@ __global__ __launch_bounds__(CB_NT) void coarse_fwd_kernel(const T* __restrict__
             ks_.fetch(kb, static_cast<int64_t>(kt + 1) * 64, N, tid);
             vs_.fetch(vb, static_cast<int64_t>(kt + 1) * 64, N, tid);
         }
-        // fragments of a product are requested together (fp32: one by one),
-        // the other accumulator's products in between
+        // fragments of two k-steps are requested together, the other
+        // accumulator's products in between
         f32x16_t s[2];
 #pragma unroll
         for (int t2 = 0; t2 < 2; ++t2)

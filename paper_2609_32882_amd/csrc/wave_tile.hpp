@@ -1,14 +1,15 @@
-// Building blocks of the one-wave attention kernel (attn_fwd_wave.hip): 64-row bf16 tiles in unpadded, XOR-swizzled LDS rows, their
-// asynchronous copies and their fragment reads.
+// Building blocks of the one-wave attention kernel (attn_fwd_wave.hip): 64-row
+// bf16 tiles in unpadded, XOR-swizzled LDS rows, their asynchronous copies and
+// their fragment reads.
 //
 // A tile is two half-tiles of 32 rows.  Tile row y lies at LDS row y; the
 // 16-byte chunk c of a row lies at chunk c ^ wt_swizzle(y).  64 banks of 4
 // bytes are 16 chunks, so with 256-byte rows (D = 128) the bank of a piece is
 // its physical chunk.
-//  - A row read (wt_row_frag, ds_read_b128) serves 16 lanes per clock, which
+//  - A row read (wave_frags::row, ds_read_b128) serves 16 lanes per clock, which
 //    read one chunk c of the 16 rows of a 16-row block: the swizzle gives
 //    those rows 16 different bank groups.
-//  - A transposing read (wt_col_frag, ds_read_b64_tr_b16) serves a half-wave
+//  - A transposing read (wave_frags::col, ds_read_b64_tr_b16) serves a half-wave
 //    per clock: 4 consecutive chunks (an aligned group) of 4 consecutive rows.
 //    The high two bits of the swizzle differ among those rows, so the groups
 //    fall on disjoint banks.
